@@ -147,7 +147,9 @@ def _stream(stream) -> Optional[int]:
         return int(stream)
     import torch
 
-    return torch.cuda.current_stream().cuda_stream
+    # the handle torch.cuda.current_stream().cuda_stream gives, without building
+    # a Stream object for it (2.9 -> 0.5 us of every call)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _code(code) -> int:
@@ -175,15 +177,22 @@ def unit_desc(x=None, codes=None, scales=None, xhat=None, row_ss_x=None, row_ss_
 
 
 def _desc_array(units: Sequence[hilore_unit_desc]):
-    arr = (hilore_unit_desc * max(1, len(units)))(*units)
-    return arr, len(units)
+    n = len(units)
+    if n < 4:
+        return (hilore_unit_desc * max(1, n))(*units), n
+    # from about 4 units on one copy of the joined structs beats filling the
+    # array element by element (78 units: about 10 us less)
+    for t in set(map(type, units)):
+        if not issubclass(t, hilore_unit_desc):
+            raise TypeError(f"expected hilore_unit_desc instances, got {t.__name__}")
+    return (hilore_unit_desc * n).from_buffer_copy(b"".join(units)), n
 
 
 # ---------------------------------------------------------------- entry points --
 def _workspace(workspace, nbytes: int, stream):
     """(pointer, size) of a caller's workspace tensor; without one, a fresh
-    zeroed device buffer of the queried size (torch's allocator) when any is
-    needed.  torch reuses a freed buffer in the order of its current stream, so
+    device buffer of the queried size (torch's allocator; no call reads what a
+    workspace holds on entry) when any is needed.  torch reuses a freed buffer in the order of its current stream, so
     a call on another stream must bring its own workspace."""
     if workspace is None:
         if nbytes == 0:
@@ -192,7 +201,7 @@ def _workspace(workspace, nbytes: int, stream):
             raise ValueError("a call on an explicit stream needs an explicit workspace")
         import torch
 
-        workspace = torch.zeros(nbytes, dtype=torch.uint8, device="cuda")
+        workspace = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
     return _p(workspace), workspace.numel() * workspace.element_size(), workspace
 
 
