@@ -256,6 +256,25 @@ hilore_status hilore_dequant_wgrad(const void *x_codes, const float *x_scales, i
                                    int64_t M, int64_t N, int accumulate, void *stream);
 
 /*
+ * hilore_dequant_wgrad with a workspace: where the 256x256 tiles of dW do not
+ * fill whole rounds of the chip's 256 CUs, the tiles of the last round are
+ * split over the tokens, their fp32 partial sums go to `workspace` and are
+ * added in ascending token order (no floating-point atomics; the split depends
+ * on K, M and N alone, so repeated calls give identical bits; against
+ * hilore_dequant_wgrad the rounding of those tiles' sums differs).  Same
+ * arguments otherwise, same limits and errors.
+ * workspace: device memory of at least hilore_wgrad_workspace_bytes(K, M, N) bytes
+ * (at most 128 MB; 0, and then NULL is allowed, where nothing is split), 16-byte
+ * aligned, contents on entry irrelevant; calls sharing it must not overlap.  Too
+ * small -> WORKSPACE.
+ */
+size_t hilore_wgrad_workspace_bytes(int64_t K, int64_t M, int64_t N);
+hilore_status hilore_dequant_wgrad_ws(const void *x_codes, const float *x_scales, int code,
+                                      int block, const uint16_t *dy, float *dw, int64_t K,
+                                      int64_t M, int64_t N, int accumulate, void *workspace,
+                                      size_t workspace_bytes, void *stream);
+
+/*
  * Gradient of the LoRA down-projection A of a linear layer whose saved input X
  * is an L unit, with the reconstruction fused into the operand load (the
  * paper's default training setting: rank-16 adapters, alpha = 32, on q/k/v/o

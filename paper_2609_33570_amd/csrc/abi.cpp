@@ -197,6 +197,41 @@ hilore_status run_exposure_risk(const float *coeff, const uint8_t *mask, int64_t
                                              exposure, risk, rel_err, s));
 }
 
+hilore_status check_wgrad(const void *x_codes, const float *x_scales, int code, int block,
+                          const uint16_t *dy, const float *dw, int64_t K, int64_t M, int64_t N) {
+  if (K < 0 || M < 0 || N < 0) return HILORE_ERR_INVALID_ARG;
+  const hilore_status cb = check_code_block(code, block);
+  if (cb != HILORE_OK) return cb;
+  const bool cast = code == HILORE_CODE_FP8_E4M3FN_CAST;
+  if ((!cast && M % block != 0) || M % 8 != 0 || N % 8 != 0) return HILORE_ERR_UNSUPPORTED;
+  if (M / 256 + 1 > (1 << 14) || N / 256 + 1 > (1 << 14)) return HILORE_ERR_UNSUPPORTED;
+  if (M == 0 || N == 0) return HILORE_OK;
+  if (!dw) return HILORE_ERR_INVALID_ARG;
+  if (K > 0 && (!x_codes || (!cast && !x_scales) || !dy)) return HILORE_ERR_INVALID_ARG;
+  const void *ptrs[] = {x_codes, x_scales, dy, dw};
+  for (const void *p : ptrs)
+    if (p && !aligned16(p)) return HILORE_ERR_ALIGNMENT;
+  return HILORE_OK;
+}
+
+hilore_status run_wgrad(const void *x_codes, const float *x_scales, int code, int block,
+                        const uint16_t *dy, float *dw, int64_t K, int64_t M, int64_t N,
+                        int accumulate, const hilore::WgradPlan &plan, float *part, void *stream) {
+  hilore::WgradArgs a{};
+  a.codes = static_cast<const uint8_t *>(x_codes);
+  a.scales = code == HILORE_CODE_FP8_E4M3FN_CAST ? nullptr : x_scales;
+  a.dy = dy;
+  a.dw = dw;
+  a.K = K;
+  a.M = M;
+  a.N = N;
+  a.accumulate = accumulate ? 1 : 0;
+  a.whole = plan.whole;
+  a.parts = plan.parts;
+  a.part = part;
+  return hip_status(hilore::launch_wgrad(a, code, block, static_cast<hipStream_t>(stream)));
+}
+
 }  // namespace
 
 extern "C" {
@@ -330,28 +365,32 @@ hilore_status hilore_unit_exposure_risk_noalloc(const float *coeff, const uint8_
 hilore_status hilore_dequant_wgrad(const void *x_codes, const float *x_scales, int code,
                                    int block, const uint16_t *dy, float *dw, int64_t K,
                                    int64_t M, int64_t N, int accumulate, void *stream) {
-  if (K < 0 || M < 0 || N < 0) return HILORE_ERR_INVALID_ARG;
-  const hilore_status cb = check_code_block(code, block);
-  if (cb != HILORE_OK) return cb;
-  const bool cast = code == HILORE_CODE_FP8_E4M3FN_CAST;
-  if ((!cast && M % block != 0) || M % 8 != 0 || N % 8 != 0) return HILORE_ERR_UNSUPPORTED;
-  if (M / 256 + 1 > (1 << 14) || N / 256 + 1 > (1 << 14)) return HILORE_ERR_UNSUPPORTED;
-  if (M == 0 || N == 0) return HILORE_OK;
-  if (!dw) return HILORE_ERR_INVALID_ARG;
-  if (K > 0 && (!x_codes || (!cast && !x_scales) || !dy)) return HILORE_ERR_INVALID_ARG;
-  const void *ptrs[] = {x_codes, x_scales, dy, dw};
-  for (const void *p : ptrs)
-    if (p && !aligned16(p)) return HILORE_ERR_ALIGNMENT;
-  hilore::WgradArgs a{};
-  a.codes = static_cast<const uint8_t *>(x_codes);
-  a.scales = cast ? nullptr : x_scales;
-  a.dy = dy;
-  a.dw = dw;
-  a.K = K;
-  a.M = M;
-  a.N = N;
-  a.accumulate = accumulate ? 1 : 0;
-  return hip_status(hilore::launch_wgrad(a, code, block, static_cast<hipStream_t>(stream)));
+  const hilore_status st = check_wgrad(x_codes, x_scales, code, block, dy, dw, K, M, N);
+  if (st != HILORE_OK || M == 0 || N == 0) return st;
+  hilore::WgradPlan whole{};
+  whole.whole = (int)(((M + 255) / 256) * ((N + 255) / 256));
+  whole.parts = 1;
+  return run_wgrad(x_codes, x_scales, code, block, dy, dw, K, M, N, accumulate, whole, nullptr,
+                   stream);
+}
+
+size_t hilore_wgrad_workspace_bytes(int64_t K, int64_t M, int64_t N) {
+  if (K <= 0 || M <= 0 || N <= 0 || M / 256 + 1 > (1 << 14) || N / 256 + 1 > (1 << 14)) return 0;
+  return hilore::wgrad_plan(K, M, N).workspace_bytes;
+}
+
+hilore_status hilore_dequant_wgrad_ws(const void *x_codes, const float *x_scales, int code,
+                                      int block, const uint16_t *dy, float *dw, int64_t K,
+                                      int64_t M, int64_t N, int accumulate, void *workspace,
+                                      size_t workspace_bytes, void *stream) {
+  const hilore_status st = check_wgrad(x_codes, x_scales, code, block, dy, dw, K, M, N);
+  if (st != HILORE_OK || M == 0 || N == 0) return st;
+  const hilore::WgradPlan plan = hilore::wgrad_plan(K, M, N);
+  if (plan.workspace_bytes > 0 && !workspace) return HILORE_ERR_INVALID_ARG;
+  if (workspace && !aligned16(workspace)) return HILORE_ERR_ALIGNMENT;
+  if (workspace_bytes < plan.workspace_bytes) return HILORE_ERR_WORKSPACE;
+  return run_wgrad(x_codes, x_scales, code, block, dy, dw, K, M, N, accumulate, plan,
+                   static_cast<float *>(workspace), stream);
 }
 
 size_t hilore_allocate_workspace_bytes(int n_units, int n_b, int n_d) {

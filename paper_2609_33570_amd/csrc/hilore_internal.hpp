@@ -122,7 +122,16 @@ struct WgradArgs {
   float *dw;
   int64_t K, M, N;
   int accumulate;
+  int whole, parts;  // tiles run whole; token parts of each other tile
+  float *part;       // workspace: one 256x256 fp32 slot per (split tile, part)
 };
+constexpr int kWgradCus = 256;       // workgroups of one round (one per CU)
+constexpr int kWgradMaxSlots = 512;  // bounds the workspace (128 MB)
+struct WgradPlan {
+  int whole, parts;
+  size_t workspace_bytes;  // 0: nothing is split
+};
+WgradPlan wgrad_plan(int64_t K, int64_t M, int64_t N);
 hipError_t launch_wgrad(const WgradArgs &a, int code, int block, hipStream_t s);
 
 // Joint H/L/R allocation (App. B.2).  Per-unit arrays are device pointers.

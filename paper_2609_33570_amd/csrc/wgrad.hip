@@ -47,6 +47,11 @@
 // launch index is remapped so that each XCD receives a contiguous run of
 // tiles, and runs are laid out 8 tile-rows tall, so the 32 CUs of an XCD share
 // X and dY panels in their own L2.
+// One workgroup fills a CU, so tiles run in rounds of 256.  With a workspace
+// the tiles past the last whole round are split over the tokens into parts,
+// one workgroup each, dispatched after the whole tiles; a part stores its
+// fp32 sums to its own slot and wgrad_reduce_kernel adds a tile's parts in
+// ascending token order (see wgrad_plan for when and how far).
 #include "device_common.hpp"
 #include "hilore_internal.hpp"
 
@@ -63,6 +68,7 @@ constexpr int kTileBytes = BM * BK * 2;  // one operand stage in LDS (32 KB)
 constexpr int kGroupM = 8;
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 // Byte offset of 16-byte granule g (t = 8g..8g+7) of row r in a [256][64] tile.
@@ -330,8 +336,17 @@ __device__ __forceinline__ void stage(f32x16 (&acc)[4][2], Frags &f, const uint8
   region<CODE, 3>(acc, f, cur_a, cur_b, nxt_a, nxt_b, raw, ry, rx, lp, fp, wave, lc, g);
 }
 
+// Tile (tm, tn) of the tile order: runs 8 tile-rows tall.
+__device__ __forceinline__ void tile_of(int id, int tiles_m, int tiles_n, int &tm, int &tn) {
+  const int per_group = kGroupM * tiles_n;
+  const int first_m = (id / per_group) * kGroupM;
+  const int gm = tiles_m - first_m < kGroupM ? tiles_m - first_m : kGroupM;
+  tm = first_m + (id % per_group) % gm;
+  tn = (id % per_group) / gm;
+}
+
 template <int CODE, int BLOCK>
-__global__ __launch_bounds__(kThreads, 1) void wgrad_kernel(const WgradArgs a, int tiles_m,
+__global__ __launch_bounds__(kThreads, 1) void wgrad_kernel(WgradArgs a, int tiles_m,
                                                             int tiles_n) {
   // Two stage buffers, each an A (dequantised X) and a B (dY) tile; separate
   // arrays so that the compiler can tell the DMA targets from the tiles
@@ -341,15 +356,30 @@ __global__ __launch_bounds__(kThreads, 1) void wgrad_kernel(const WgradArgs a, i
   __shared__ __attribute__((aligned(16))) uint8_t lds_a1[kTileBytes];
   __shared__ __attribute__((aligned(16))) uint8_t lds_b1[kTileBytes];
 
-  // XCD-aware tile order.
-  const int n_wg = tiles_m * tiles_n;
+  // XCD-aware order of the whole tiles, then of the (part, tile) pairs of the
+  // split ones, parts slowest: neighbours share the X or dY rows of one part.
   int id = blockIdx.x;
-  if ((n_wg & 7) == 0) id = (id & 7) * (n_wg >> 3) + (id >> 3);
-  const int per_group = kGroupM * tiles_n;
-  const int first_m = (id / per_group) * kGroupM;
-  const int gm = tiles_m - first_m < kGroupM ? tiles_m - first_m : kGroupM;
-  const int tm = first_m + (id % per_group) % gm;
-  const int tn = (id % per_group) / gm;
+  float *slot = nullptr;  // a split tile's part: where its sums go
+  if (id < a.whole) {
+    if ((a.whole & 7) == 0) id = (id & 7) * (a.whole >> 3) + (id >> 3);
+  } else {
+    const int rem = tiles_m * tiles_n - a.whole, n = rem * a.parts;
+    const int i = id - a.whole, x = i & 7, q = n >> 3, r = n & 7;
+    const int w = x * q + (x < r ? x : r) + (i >> 3);
+    const int part = w / rem, t = w - part * rem;
+    id = a.whole + t;
+    slot = a.part + ((int64_t)t * a.parts + part) * (BM * BN);
+    // this part's tokens: whole pairs of stages, the last part up to K
+    const int64_t pairs = (a.K + 2 * BK - 1) / (2 * BK);
+    const int64_t k0 = pairs * part / a.parts * (2 * BK);
+    const int64_t k1 = pairs * (part + 1) / a.parts * (2 * BK);
+    a.codes += k0 * a.M;
+    if constexpr (CODE != kCodeCast) a.scales += k0 * (a.M / BLOCK);
+    a.dy += k0 * a.N;
+    a.K = (k1 < a.K ? k1 : a.K) - k0;
+  }
+  int tm, tn;
+  tile_of(id, tiles_m, tiles_n, tm, tn);
   const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
 
   const int tid = threadIdx.x;
@@ -424,31 +454,72 @@ __global__ __launch_bounds__(kThreads, 1) void wgrad_kernel(const WgradArgs a, i
                        wave, lc, g);
   }
 
+  // A part's sums go to its slot, a dense 256x256 tile.
+  const bool split = slot != nullptr;
+  float *const out = split ? slot : a.dw + m0 * a.N + n0;
+  const int64_t ld = split ? BN : a.N;
+  const int64_t rows = split ? BM : a.M - m0, cols = split ? BN : a.N - n0;
+  const bool add = a.accumulate && !split;
+
   // Epilogue.  32x32 accumulator layout: lane l holds column l % 32 and, for
   // register r, row 8 (r / 4) + 4 (l / 32) + r % 4.
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      const int64_t col = n0 + wn * 64 + j * 32 + fp.lrow;
+      const int col = wn * 64 + j * 32 + fp.lrow;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const int64_t row = m0 + fp.wm * 128 + i * 32 + (r >> 2) * 8 + fp.lk * 4 + (r & 3);
-        if (row < a.M && col < a.N) {
-          float *p = a.dw + row * a.N + col;
-          *p = a.accumulate ? *p + acc[i][j][r] : acc[i][j][r];
+        const int row = fp.wm * 128 + i * 32 + (r >> 2) * 8 + fp.lk * 4 + (r & 3);
+        if (row < rows && col < cols) {
+          float *p = out + row * ld + col;
+          *p = add ? *p + acc[i][j][r] : acc[i][j][r];
         }
       }
     }
   }
 }
 
+// dW (+)= the parts of one split tile in ascending token order, four
+// neighbouring columns per thread, up to 8 parts in flight.
+constexpr int kReduceBatch = 8;
+
+__global__ __launch_bounds__(256) void wgrad_reduce_kernel(const WgradArgs a, int tiles_m,
+                                                           int tiles_n) {
+  constexpr int kQuads = BM * BN / 4;
+  const int t = (int)(blockIdx.x / (kQuads / 256));
+  const int e = ((int)(blockIdx.x % (kQuads / 256)) * 256 + (int)threadIdx.x) * 4;
+  int tm, tn;
+  tile_of(a.whole + t, tiles_m, tiles_n, tm, tn);
+  const int64_t row = (int64_t)tm * BM + e / BN, col = (int64_t)tn * BN + e % BN;
+  if (row >= a.M || col >= a.N) return;  // N % 8 == 0: the 4 columns are all inside
+  const float *src = a.part + (int64_t)t * a.parts * (BM * BN) + e;
+  f32x4 sum = *reinterpret_cast<const f32x4 *>(src);
+  for (int p = 1; p < a.parts; p += kReduceBatch) {
+    f32x4 x[kReduceBatch];
+#pragma unroll
+    for (int k = 0; k < kReduceBatch; ++k)
+      x[k] = p + k < a.parts
+                 ? *reinterpret_cast<const f32x4 *>(src + (int64_t)(p + k) * (BM * BN))
+                 : f32x4{};
+#pragma unroll
+    for (int k = 0; k < kReduceBatch; ++k)
+      if (p + k < a.parts) sum += x[k];
+  }
+  f32x4 *out = reinterpret_cast<f32x4 *>(a.dw + row * a.N + col);  // 16-byte aligned: N % 8 == 0
+  *out = a.accumulate ? *out + sum : sum;
+}
+
 template <int CODE, int BLOCK>
 hipError_t launch_one(const WgradArgs &a, hipStream_t s) {
   const int tiles_m = (int)((a.M + BM - 1) / BM);
   const int tiles_n = (int)((a.N + BN - 1) / BN);
-  hipLaunchKernelGGL((wgrad_kernel<CODE, BLOCK>), dim3(tiles_m * tiles_n), dim3(kThreads), 0, s,
-                     a, tiles_m, tiles_n);
+  const int rem = tiles_m * tiles_n - a.whole;
+  hipLaunchKernelGGL((wgrad_kernel<CODE, BLOCK>), dim3(a.whole + rem * a.parts), dim3(kThreads), 0,
+                     s, a, tiles_m, tiles_n);
+  if (rem > 0)
+    hipLaunchKernelGGL(wgrad_reduce_kernel, dim3(rem * (BM * BN / 1024)), dim3(256), 0, s, a,
+                       tiles_m, tiles_n);
   return hipGetLastError();
 }
 
@@ -463,6 +534,46 @@ hipError_t dispatch(const WgradArgs &a, int block, hipStream_t s) {
 }
 
 }  // namespace
+
+// How many tiles run whole and into how many parts the others are split.
+// Rounds of 256 whole tiles stay whole.  The rest (all tiles below 256) would
+// leave CUs idle for a whole tile's time, so it is split into the number of
+// parts with the least estimated time: rounds of parts, each its stages plus
+// a fixed pipeline fill and drain, and one more launch that reads the partial
+// sums.  The constants are measured (us): a stage takes 1.75 with all CUs busy
+// and about 1.25 with few (the chip then clocks higher, so idle CUs cost less
+// than their share: 896 tiles gain 2%, not the 13% of the empty half round),
+// the slots' round trip through memory 0.06 each.  A split has to promise a
+// tenth, the model's own error.
+// Unsplit -> split, fp8 1x128, us a call: 11987x3584x512 266 -> 58,
+// 16384x3584x18944 2143 -> 1862, 16384x896x4864 333 -> 157,
+// 1024x896x256 28 -> 19; 1024x3584x512 would stay at 29.
+WgradPlan wgrad_plan(int64_t K, int64_t M, int64_t N) {
+  constexpr double kStageUs = 1.25, kBusyUs = 0.5, kFillUs = 8.0, kReduceUs = 8.0, kSlotUs = 0.06;
+  WgradPlan p{};
+  const int64_t tiles = ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
+  p.whole = (int)tiles;
+  p.parts = 1;
+  const int rem = (int)(tiles % kWgradCus);
+  const int64_t pairs = (K + 2 * BK - 1) / (2 * BK);
+  if (rem == 0 || pairs < 2) return p;
+  auto part_us = [&](int n) {  // one round of n parts per tile
+    const int busy = rem * n < kWgradCus ? rem * n : kWgradCus;
+    return 2.0 * (double)((pairs + n - 1) / n) * (kStageUs + kBusyUs * busy / kWgradCus) + kFillUs;
+  };
+  double best = 0.9 * part_us(1);
+  for (int n = 2; n <= pairs && n * rem <= kWgradMaxSlots; ++n) {
+    const int rounds = (rem * n + kWgradCus - 1) / kWgradCus;
+    const double us = rounds * part_us(n) + kReduceUs + kSlotUs * rem * n;
+    if (us < best) {
+      best = us;
+      p.whole = (int)tiles - rem;
+      p.parts = n;
+    }
+  }
+  if (p.parts > 1) p.workspace_bytes = (size_t)rem * p.parts * BM * BN * sizeof(float);
+  return p;
+}
 
 hipError_t launch_wgrad(const WgradArgs &a, int code, int block, hipStream_t s) {
   if (a.M == 0 || a.N == 0) return hipSuccess;

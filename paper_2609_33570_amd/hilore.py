@@ -80,6 +80,9 @@ def load() -> ctypes.CDLL:
                                             ctypes.c_size_t, P]),
         "hilore_unit_exposure_risk_noalloc": (i32, [P, P, i64, P, i32, f32, f32, P, P, P, P]),
         "hilore_dequant_wgrad": (i32, [P, P, i32, i32, P, P, i64, i64, i64, i32, P]),
+        "hilore_wgrad_workspace_bytes": (ctypes.c_size_t, [i64, i64, i64]),
+        "hilore_dequant_wgrad_ws": (i32, [P, P, i32, i32, P, P, i64, i64, i64, i32, P,
+                                          ctypes.c_size_t, P]),
         "hilore_allocate_workspace_bytes": (ctypes.c_size_t, [i32, i32, i32]),
         "hilore_allocate": (i32, [i32, P, P, P, P, P, P, P, f64, f64, i32, i32, P, P, P, P,
                                   ctypes.c_size_t, P]),
@@ -269,12 +272,35 @@ def hilore_unit_exposure_risk_noalloc(coeff, mask, rows: int, units: Sequence[hi
                                                     _stream(stream)))
 
 
+def hilore_wgrad_workspace_bytes(K: int, M: int, N: int) -> int:
+    return int(load().hilore_wgrad_workspace_bytes(int(K), int(M), int(N)))
+
+
 def hilore_dequant_wgrad(x_codes, x_scales, code, block: int, dy, dw, K: int, M: int, N: int,
-                         accumulate: bool = False, stream=None):
-    _check("hilore_dequant_wgrad",
-           load().hilore_dequant_wgrad(_p(x_codes), _p(x_scales), _code(code), int(block),
-                                       _p(dy), _p(dw), int(K), int(M), int(N),
-                                       1 if accumulate else 0, _stream(stream)))
+                         accumulate: bool = False, stream=None, workspace=None):
+    """workspace: a device tensor of at least hilore_wgrad_workspace_bytes(K, M, N) bytes
+    for the partial sums of split tiles.  None: a buffer of that size from torch's
+    allocator, or the unsplit call where that cannot be had (an explicit stream, no
+    memory left)."""
+    L = load()
+    args = (_p(x_codes), _p(x_scales), _code(code), int(block), _p(dy), _p(dw), int(K), int(M),
+            int(N), 1 if accumulate else 0)
+    if workspace is None and stream is None:
+        need = L.hilore_wgrad_workspace_bytes(args[6], args[7], args[8])
+        if need:
+            import torch
+
+            try:
+                workspace = torch.empty(need, dtype=torch.uint8, device=dw.device)
+            except torch.cuda.OutOfMemoryError:
+                pass
+    if workspace is None:
+        st = L.hilore_dequant_wgrad(*args, _stream(stream))
+    else:
+        st = L.hilore_dequant_wgrad_ws(*args, _p(workspace),
+                                       workspace.numel() * workspace.element_size(),
+                                       _stream(stream))
+    _check("hilore_dequant_wgrad", st)
 
 
 def hilore_lora_grad_workspace_bytes(K: int, M: int, r: int) -> int:

@@ -1,0 +1,83 @@
+"""hilore_dequant_wgrad_ws: tiles past the last whole round split over tokens.
+
+Integer-valued operands make every partial sum an integer below 2^24, so the
+split and the unsplit call must agree bit for bit; a guard behind the workspace
+and a NaN-filled dW show writes out of place and elements left out.
+"""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2609_33570_amd import hilore as hl_mod
+
+GUARD = 4096
+
+
+def test_workspace_sizes():
+    """256 KB slots, at most 512 of them; none where the tiles fill whole rounds or K is short."""
+    need = hl_mod.hilore_wgrad_workspace_bytes
+    assert need(16384, 4096, 4096) == 0   # 256 tiles
+    assert need(16384, 8192, 4096) == 0   # 512 tiles
+    assert need(128, 512, 512) == 0       # one pair of stages
+    assert need(0, 512, 512) == 0 and need(16384, 0, 512) == 0
+    for K, M, N in [(16384, 3584, 512), (1024, 896, 256), (16384, 3584, 18944),
+                    (11987, 4096, 14336), (2 ** 20, 256, 8), (16384, 4104, 4096)]:
+        b = need(K, M, N)
+        tiles = -(-M // 256) * -(-N // 256)
+        assert 0 < b <= 512 << 18 and b % ((tiles % 256) << 18) == 0, (K, M, N, b)
+
+
+def test_workspace_errors():
+    """Checked on the host before anything is enqueued."""
+    L = hl_mod.load()
+    p = ctypes.c_void_p(1 << 20)
+    call = lambda ws, n: L.hilore_dequant_wgrad_ws(p, p, 1, 128, p, p, 16384, 3584, 512, 0,  # noqa: E731
+                                                   ws, n, None)
+    need = hl_mod.hilore_wgrad_workspace_bytes(16384, 3584, 512)
+    assert call(None, 0) == hl_mod.HILORE_ERR_INVALID_ARG
+    assert call(ctypes.c_void_p((1 << 20) + 8), need) == hl_mod.HILORE_ERR_ALIGNMENT
+    assert call(p, need - 1) == hl_mod.HILORE_ERR_WORKSPACE
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("code,block", [(0, 64), (1, 128), (2, 0)], ids=["int8", "e4m3fn", "cast"])
+@pytest.mark.parametrize("K,M,N", [
+    (1025, 256, 8),       # the last part one token, 8 columns of a tile
+    (1000, 768, 272),     # ragged in K and N
+    (4095, 128, 1032),    # half a tile of rows
+    (16384, 3584, 512),   # 28 tiles
+    (2000, 4352, 4096),   # 272 tiles: 256 whole, 16 split
+    (2100, 3968, 4360),   # 288 tiles, ragged
+])
+@pytest.mark.parametrize("accumulate", [False, True], ids=["write", "add"])
+def test_split_matches_unsplit(hl, code, block, K, M, N, accumulate):
+    g = torch.Generator(device="cuda").manual_seed(K + M + N)
+    x = torch.randint(-7, 8, (K, M), generator=g, device="cuda").to(torch.bfloat16)
+    dy = torch.randint(-8, 9, (K, N), generator=g, device="cuda").to(torch.bfloat16)
+    if code == 0:
+        codes = (x.to(torch.int8) * 16).view(torch.uint8)
+        scales = torch.full((K, M // block), 1 / 16, device="cuda")
+    else:
+        codes = x.to(torch.float8_e4m3fn).view(torch.uint8)
+        scales = torch.full((K, M // block), 1.0, device="cuda") if block else None
+    need = hl.hilore_wgrad_workspace_bytes(K, M, N)
+    assert need > 0
+    dw0 = (torch.randint(-50, 51, (M, N), generator=g, device="cuda").float() if accumulate
+           else torch.full((M, N), float("nan"), device="cuda"))
+    buf = torch.full((need + GUARD,), 0xA5, dtype=torch.uint8, device="cuda")
+    stream = torch.cuda.current_stream().cuda_stream
+    want, given, auto = dw0.clone(), dw0.clone(), dw0.clone()
+    # an explicit stream without a workspace: the unsplit call
+    hl.hilore_dequant_wgrad(codes, scales, code, block, dy, want, K, M, N, accumulate, stream=stream)
+    hl.hilore_dequant_wgrad(codes, scales, code, block, dy, given, K, M, N, accumulate,
+                            workspace=buf[:need])
+    hl.hilore_dequant_wgrad(codes, scales, code, block, dy, auto, K, M, N, accumulate)
+    torch.cuda.synchronize()
+    ref = x[:, :8].double().t().contiguous() @ dy.double()
+    if accumulate:
+        ref += dw0[:8].double()
+    assert np.array_equal(want[:8].double().cpu().numpy(), ref.cpu().numpy())
+    assert torch.equal(given, want) and torch.equal(auto, want)
+    assert bool((buf[need:] == 0xA5).all())
