@@ -45,10 +45,23 @@
 // MFMA c accumulates dA[4h + v][16q' + c] in lane (q', h), register v; at a
 // segment end the 8 waves' accumulators are summed through LDS in wave order.
 //
-// Passes of 17 .. 80 adapter rows (R = 2 .. 5 blocks of 16): lora_coop_kernel.
-// Per-wave accumulators for 16 R rows x 256 columns would not fit the register
-// file, so the workgroup walks its k-steps in order, two per barrier: every
-// thread loads 16 code bytes of each (D k-steps in flight in registers) and
+// Passes of 17 .. 64 adapter rows (R = 2 .. 4 blocks of 16): lora_slab_kernel.
+// Accumulators for 16 R rows x 256 columns would not fit one wave's registers,
+// so a k-step of a strip is shared by a pair of waves, 128 columns each (8-byte
+// code loads, 32 R accumulator registers), four pairs taking every 4th k-step on
+// their own.  dh and the scale list go to the wave's own LDS by LDS-DMA, so two
+// k-steps in flight cost registers for their codes only; no barrier until the
+// segment end, where the pairs' sums are added through LDS in order.  What is
+// left is traffic: without the MFMAs and the dequantisation it runs as long, and
+// four k-steps in flight change nothing; each 16 adapter rows add 6-7 us on
+// 16384 x 18944, half of it dh (R KB per 4 KB of codes), half the partial sums.
+// us a call (fp8 1x128) against the cooperative kernel, r = 32 / 48 / 64:
+// 16384 x 18944 85 / 92 / 98 against 90 / 95 / 111, 13001 x 3584 23 / 25 / 27
+// against 25 / 27 / 31.
+//
+// Passes of 65 .. 80 rows (R = 5): lora_coop_kernel (the slab kernel would need
+// 280 registers; spilling it takes 128 us against 116 on 16384 x 18944).  The
+// workgroup walks its k-steps in order, two per barrier: every thread loads 16 code bytes of each (D k-steps in flight in registers) and
 // dequantises them once into a double-buffered [64][256] bf16 tile in LDS,
 // the dh block goes to LDS next to it, and wave w runs the MFMAs of column
 // groups 2w and 2w+1 (16 columns each, B operand by transposing reads of the
@@ -358,6 +371,249 @@ __global__ __launch_bounds__(kThreads, 1) void lora_wave_kernel(const LoraArgs a
   }
 }
 
+// ------------------------------------------------------------ slab kernel --
+
+constexpr int kHalf = 128;              // columns of one wave's slab
+constexpr int kPairs = kWaves / 2;      // k-steps in progress per workgroup
+constexpr int kSlabScales = 512;        // bytes of one k-step's scale list
+
+typedef __attribute__((address_space(3))) void lds_void;
+
+// Scale blocks that meet one 128-column slab.
+template <int BLOCK>
+constexpr int kSlabBlocks = BLOCK < kHalf ? kHalf / BLOCK : 1;
+
+// Per-lane, loop-invariant parts of a wave's loads.
+template <int BLOCK, int R, bool WIDE>
+struct SlabPlan {
+  static constexpr int kDhLoads = WIDE ? R : 4 * R;               // 1 KB / 256 B each
+  static constexpr int kScLoads = (32 * kSlabBlocks<BLOCK> + 63) / 64;
+  // loads issued after a k-step's DMA when the next k-step's are in flight
+  template <int CODE>
+  static constexpr int kYounger = 8 + (kDhLoads + (CODE == kCodeCast ? 0 : kScLoads) + 8);
+  uint32_t vo_c;              // codes: row 8h, columns 8q .. 8q+7 of the slab
+  uint32_t vo_d[kDhLoads];    // dh piece lane + 64 i
+  uint32_t vo_s[kScLoads];    // scale lane + 64 i of the (block, row) list
+};
+
+// Order of a wave's own LDS-DMA and LDS reads.  The compiler takes a DMA for a
+// 16-byte store at its LDS address and so moves reads of the other bytes that it
+// fills across it: both directions are fenced by hand, and the loads of a k-step
+// stay in the order written (DMA, then codes), so that a count of younger loads
+// tells when its DMA has landed.
+__device__ __forceinline__ void order_memory() { asm volatile("" ::: "memory"); }
+__device__ __forceinline__ void reads_done() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+template <int YOUNGER>
+__device__ __forceinline__ void dma_landed() {
+  static_assert(YOUNGER < 64, "vmcnt is 6 bits");
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(YOUNGER) : "memory");
+}
+
+// Start the loads of k-step kk: dh and scales by LDS-DMA into the wave's own
+// areas (no registers; lanes past a range write 0), the codes into registers.
+template <int CODE, int BLOCK, int R, bool WIDE>
+__device__ __forceinline__ void slab_load(u32x2 (&c)[8], uint8_t *dh, uint8_t *sc,
+                                          const LoraArgs &a,
+                                          const SlabPlan<BLOCK, R, WIDE> &p, int64_t kk,
+                                          bool live) {
+  const int64_t rows = step_rows(a, kk, live);
+  const int64_t t0 = kk * kStep;
+  const __amdgpu_buffer_rsrc_t rd = dh_rsrc(a, t0, rows);
+  reads_done();
+#pragma unroll
+  for (int i = 0; i < p.kDhLoads; ++i) {
+    if constexpr (WIDE)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rd, (lds_void *)(dh + i * 1024), 16,
+                                               (int)p.vo_d[i], 0, 0, 0);
+    else
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rd, (lds_void *)(dh + i * 256), 4,
+                                               (int)p.vo_d[i], 0, 0, 0);
+  }
+  if constexpr (CODE != kCodeCast) {
+    const int64_t sld = a.M / BLOCK;
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)(a.scales + t0 * sld), 0, (int)(rows * sld * 4), 0x00020000);
+#pragma unroll
+    for (int i = 0; i < p.kScLoads; ++i)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void *)(sc + i * 256), 4,
+                                               (int)p.vo_s[i], 0, 0, 0);
+  }
+  const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(
+      (void *)(a.codes + t0 * a.M), 0, (int)(rows * a.M), 0x00020000);
+  order_memory();
+#pragma unroll
+  for (int j = 0; j < 8; ++j)
+    c[j] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(
+                                         rc, (int)(p.vo_c + j * (uint32_t)a.M), 0, kNonTemporal));
+  order_memory();
+}
+
+// Columns 4 D + C and 4 D + C + 1 of the lane's 8 for all row blocks.
+template <int CODE, int R, int D, int C>
+__device__ __forceinline__ void slab_pair(f32x4 (&acc)[R][8], const u32x2 (&cw)[8],
+                                          const float (&sc)[8], const bf16x8 (&A)[R]) {
+  float lo[8], hi[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const f32x2 v = decode_pair<CODE, C>(D == 0 ? cw[j].x : cw[j].y);
+    if constexpr (CODE == kCodeCast) {
+      lo[j] = v.x;
+      hi[j] = v.y;
+    } else {
+      lo[j] = v.x * sc[j];
+      hi[j] = v.y * sc[j];
+    }
+  }
+  const u32x4 b0 = {pack_bf16(lo[0], lo[1]), pack_bf16(lo[2], lo[3]), pack_bf16(lo[4], lo[5]),
+                    pack_bf16(lo[6], lo[7])};
+  const u32x4 b1 = {pack_bf16(hi[0], hi[1]), pack_bf16(hi[2], hi[3]), pack_bf16(hi[4], hi[5]),
+                    pack_bf16(hi[6], hi[7])};
+  constexpr int c0 = 4 * D + C;
+#pragma unroll
+  for (int rb = 0; rb < R; ++rb) {
+    acc[rb][c0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+        A[rb], __builtin_bit_cast(bf16x8, b0), acc[rb][c0], 0, 0, 0);
+    acc[rb][c0 + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+        A[rb], __builtin_bit_cast(bf16x8, b1), acc[rb][c0 + 1], 0, 0, 0);
+  }
+}
+
+// A k-step's MFMAs: dh^T by transposing reads of the staged [32][16 R] block
+// (lane 4e + a of 16-lane group h addresses row 8h + e, adapter rows 4a ..
+// 4a+3 of a block), the scales of rows 8h .. 8h+7 from the (block, row) list.
+template <int CODE, int BLOCK, int R>
+__device__ __forceinline__ void slab_step(f32x4 (&acc)[R][8], const u32x2 (&cw)[8],
+                                          const uint8_t *dh, const uint8_t *scl, int lane) {
+  const int q = lane & 15, h = lane >> 4;
+  const uint32_t tr = (uint32_t)(8 * h + (q >> 2)) * (32u * R) + (uint32_t)(q & 3) * 8u;
+  bf16x8 A[R];
+#pragma unroll
+  for (int rb = 0; rb < R; ++rb) {
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(dh + tr + 32 * rb));
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+        (lds_s16x4 *)(dh + tr + 32 * rb + 4 * 32 * R));
+    A[rb] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+  }
+  float sc[8];
+  if constexpr (CODE == kCodeCast) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) sc[j] = 1.f;
+  } else {
+    const float *f = reinterpret_cast<const float *>(scl) +
+                     (BLOCK < kHalf ? 8 * q / BLOCK : 0) * 32 + 8 * h;
+    const f32x4 s0 = *reinterpret_cast<const f32x4 *>(f);
+    const f32x4 s1 = *reinterpret_cast<const f32x4 *>(f + 4);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      sc[j] = s0[j];
+      sc[4 + j] = s1[j];
+    }
+  }
+  slab_pair<CODE, R, 0, 0>(acc, cw, sc, A);
+  __builtin_amdgcn_sched_barrier(0);
+  slab_pair<CODE, R, 0, 2>(acc, cw, sc, A);
+  __builtin_amdgcn_sched_barrier(0);
+  slab_pair<CODE, R, 1, 0>(acc, cw, sc, A);
+  __builtin_amdgcn_sched_barrier(0);
+  slab_pair<CODE, R, 1, 2>(acc, cw, sc, A);
+}
+
+template <int CODE, int BLOCK, int R, bool WIDE>
+__global__ __launch_bounds__(kThreads, 1) void lora_slab_kernel(const LoraArgs a) {
+  // one array per k-step in flight (the compiler then adds no waits of its own
+  // between one step's DMA and the other's reads)
+  __shared__ __attribute__((aligned(16))) uint8_t dh0[kWaves][1024 * R];
+  __shared__ __attribute__((aligned(16))) uint8_t dh1[kWaves][1024 * R];
+  __shared__ __attribute__((aligned(16))) uint8_t sc0[kWaves][kSlabScales];
+  __shared__ __attribute__((aligned(16))) uint8_t sc1[kWaves][kSlabScales];
+  __shared__ __attribute__((aligned(16))) float red[kWaves][kRows * kHalf];
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int lane = tid % kWave;
+  const int q = lane & 15, h = lane >> 4;
+  const int half = wave & 1, pair = wave >> 1;
+  const int64_t bid = blockIdx.x;
+  const int64_t wg = a.xcd_remap ? (bid & 7) * (a.n_wg >> 3) + (bid >> 3) : bid;
+  const int64_t u_end = range_begin(a, wg + 1);
+  constexpr int64_t kSlot = (int64_t)kRows * R * kStrip;
+
+  SlabPlan<BLOCK, R, WIDE> p;
+#pragma unroll
+  for (int i = 0; i < p.kDhLoads; ++i)
+    p.vo_d[i] = WIDE ? dh_offset(a, lane + 64 * i, 2 * R, 8) : dh_offset(a, lane + 64 * i, 8 * R, 2);
+
+  int seg = 0;
+  // at most two segments per range (the plan keeps n_wg >= S)
+  for (int64_t u = range_begin(a, wg); u < u_end && seg < 2; ++seg) {
+    const int64_t s = u / a.KS;
+    const int64_t k_end = (u_end - s * a.KS) < a.KS ? (u_end - s * a.KS) : a.KS;
+    const int64_t col = s * kStrip + half * kHalf + 8 * q;
+    p.vo_c = col < a.M ? (uint32_t)(8 * h) * (uint32_t)a.M + (uint32_t)col : kOob;
+#pragma unroll
+    for (int i = 0; i < p.kScLoads; ++i) {
+      const int e = 64 * i + lane;  // scale of row e % 32 of the slab's block e / 32
+      const int64_t blk = (s * kStrip + half * kHalf) / BLOCK + e / 32;
+      p.vo_s[i] = e < 32 * kSlabBlocks<BLOCK> && blk * BLOCK < a.M
+                      ? (uint32_t)(e % 32) * (uint32_t)(a.M / BLOCK) * 4u + (uint32_t)blk * 4u
+                      : kOob;
+    }
+
+    f32x4 acc[R][8];
+#pragma unroll
+    for (int rb = 0; rb < R; ++rb)
+#pragma unroll
+      for (int c = 0; c < 8; ++c) acc[rb][c] = f32x4{};
+    // this wave's k-steps kk, kk + 4, ...; two in flight (an odd count ends
+    // with a step whose loads are empty: zeros, its MFMAs add nothing)
+    int64_t kk = u - s * a.KS + pair;
+    u32x2 w0[8], w1[8];
+    slab_load<CODE, BLOCK, R, WIDE>(w0, dh0[wave], sc0[wave], a, p, kk, kk < k_end);
+    slab_load<CODE, BLOCK, R, WIDE>(w1, dh1[wave], sc1[wave], a, p, kk + kPairs,
+                                    kk + kPairs < k_end);
+    const int64_t n = kk < k_end ? (k_end - kk + 2 * kPairs - 1) / (2 * kPairs) : 0;
+    for (int64_t i = 0; i < n; ++i) {
+      dma_landed<SlabPlan<BLOCK, R, WIDE>::template kYounger<CODE>>();
+      slab_step<CODE, BLOCK, R>(acc, w0, dh0[wave], sc0[wave], lane);
+      slab_load<CODE, BLOCK, R, WIDE>(w0, dh0[wave], sc0[wave], a, p, kk + 2 * kPairs,
+                                      kk + 2 * kPairs < k_end);
+      dma_landed<SlabPlan<BLOCK, R, WIDE>::template kYounger<CODE>>();
+      slab_step<CODE, BLOCK, R>(acc, w1, dh1[wave], sc1[wave], lane);
+      slab_load<CODE, BLOCK, R, WIDE>(w1, dh1[wave], sc1[wave], a, p, kk + 3 * kPairs,
+                                      kk + 3 * kPairs < k_end);
+      kk += 2 * kPairs;
+    }
+
+    // acc[rb][c][v] = dA[16 rb + 4h + v][128 half + 8 q + c] of this wave's
+    // k-steps; the four pairs are added in order, one row block at a time
+    float *out = a.part + (2 * wg + seg) * kSlot;
+#pragma unroll
+    for (int rb = 0; rb < R; ++rb) {
+      float *mine = red[wave];
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int c4 = 0; c4 < 2; ++c4)
+          *reinterpret_cast<f32x4 *>(&mine[(4 * h + v) * kHalf + 8 * q + 4 * c4]) =
+              f32x4{acc[rb][4 * c4][v], acc[rb][4 * c4 + 1][v], acc[rb][4 * c4 + 2][v],
+                    acc[rb][4 * c4 + 3][v]};
+      __syncthreads();
+#pragma unroll
+      for (int e4 = 0; e4 < kPart / 4 / kThreads; ++e4) {
+        const int e = 4 * (tid + e4 * kThreads);
+        const int row = e / kStrip, c = e % kStrip, hf = c / kHalf;
+        const int at = row * kHalf + c % kHalf;
+        f32x4 sum = *reinterpret_cast<const f32x4 *>(&red[hf][at]);
+#pragma unroll
+        for (int w = 1; w < kPairs; ++w)
+          sum += *reinterpret_cast<const f32x4 *>(&red[2 * w + hf][at]);
+        *reinterpret_cast<f32x4 *>(out + rb * kPart + e) = sum;
+      }
+      __syncthreads();
+    }
+    u = (s + 1) * a.KS;
+  }
+}
+
 // ------------------------------------------------------ cooperative kernel --
 
 // One thread's operands of a k-step: codes of row tid / 16, columns
@@ -616,13 +872,13 @@ void launch_main(const LoraArgs &a, hipStream_t s) {
       hipLaunchKernelGGL((lora_wave_kernel<CODE, BLOCK, WIDE>), grid, block, 0, s, a);
       return;
     case 2:
-      hipLaunchKernelGGL((lora_coop_kernel<CODE, BLOCK, 2, WIDE>), grid, block, 0, s, a);
+      hipLaunchKernelGGL((lora_slab_kernel<CODE, BLOCK, 2, WIDE>), grid, block, 0, s, a);
       return;
     case 3:
-      hipLaunchKernelGGL((lora_coop_kernel<CODE, BLOCK, 3, WIDE>), grid, block, 0, s, a);
+      hipLaunchKernelGGL((lora_slab_kernel<CODE, BLOCK, 3, WIDE>), grid, block, 0, s, a);
       return;
     case 4:
-      hipLaunchKernelGGL((lora_coop_kernel<CODE, BLOCK, 4, WIDE>), grid, block, 0, s, a);
+      hipLaunchKernelGGL((lora_slab_kernel<CODE, BLOCK, 4, WIDE>), grid, block, 0, s, a);
       return;
     default:
       hipLaunchKernelGGL((lora_coop_kernel<CODE, BLOCK, 5, WIDE>), grid, block, 0, s, a);
