@@ -40,7 +40,9 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kSlotsPerThread = 4;
 constexpr int kSlotsPerBlock = kThreads * kSlotsPerThread;
-constexpr int kMaxResp = kSlotsPerBlock + 2;  // responses overlapping one run (T >= 1)
+constexpr int kCountThreads = 1024;  // pre-pass: 2^16 slots are four mask words per thread
+constexpr int kCountBatch = 4;
+constexpr int64_t kTwoRunSlots = int64_t(1) << 20;  // from here on two runs per workgroup
 constexpr int kMaskBatch = 8;  // 16-byte mask words per thread in flight while counting
 static_assert(kGrpoCounts <= kThreads, "one pre-pass count per thread");
 
@@ -61,83 +63,111 @@ __device__ __forceinline__ uint32_t nonzero_bytes(uint32_t w) {
 // Count of the nonzero bytes of mask words [w0, w1) plus, in the last
 // workgroup, of the bytes past the last whole word; one 32-bit count per
 // workgroup.
-__global__ __launch_bounds__(kThreads) void count_kernel(const uint8_t *mask, int64_t n_slots,
+__global__ __launch_bounds__(kCountThreads) void count_kernel(const uint8_t *mask, int64_t n_slots,
                                                          int64_t words_per_wg, uint32_t *counts) {
-  __shared__ uint32_t red[kThreads / kWave];
+  __shared__ uint32_t red[kCountThreads / kWave];
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   const int64_t n_words = n_slots / 16;
   const int64_t w0 = (int64_t)blockIdx.x * words_per_wg;
   const int64_t w1 = w0 + words_per_wg < n_words ? w0 + words_per_wg : n_words;
   const uint4 *m4 = reinterpret_cast<const uint4 *>(mask);
   uint32_t cnt = 0;
-  for (int64_t base = w0; base < w1; base += kMaskBatch * kThreads) {
-    uint4 mw[kMaskBatch];
+  for (int64_t base = w0; base < w1; base += kCountBatch * kCountThreads) {
+    uint4 mw[kCountBatch];
 #pragma unroll
-    for (int u = 0; u < kMaskBatch; ++u) {
-      const int64_t i = base + (int64_t)u * kThreads + tid;
+    for (int u = 0; u < kCountBatch; ++u) {
+      const int64_t i = base + (int64_t)u * kCountThreads + tid;
       mw[u] = i < w1 ? m4[i] : make_uint4(0u, 0u, 0u, 0u);
     }
 #pragma unroll
-    for (int u = 0; u < kMaskBatch; ++u)
+    for (int u = 0; u < kCountBatch; ++u)
       cnt += nonzero_bytes(mw[u].x) + nonzero_bytes(mw[u].y) + nonzero_bytes(mw[u].z) +
              nonzero_bytes(mw[u].w);
   }
   if (blockIdx.x == gridDim.x - 1)
-    for (int64_t i = n_words * 16 + tid; i < n_slots; i += kThreads) cnt += mask[i] != 0;
+    for (int64_t i = n_words * 16 + tid; i < n_slots; i += kCountThreads) cnt += mask[i] != 0;
   for (int off = 1; off < kWave; off <<= 1) cnt += __shfl_xor(cnt, off, kWave);
   if (lane == 0) red[wave] = cnt;
   __syncthreads();
-  if (tid == 0) counts[blockIdx.x] = red[0] + red[1] + red[2] + red[3];
+  if (tid == 0) {
+    uint32_t n = 0;
+#pragma unroll
+    for (int w = 0; w < kCountThreads / kWave; ++w) n += red[w];
+    counts[blockIdx.x] = n;
+  }
 }
 
+// expm1 for |x| <= 1/2: the Taylor polynomial to x^8 (its remainder is below
+// 2^-26 of x there) closed by one rounding of x + x^2 P(x); 9 instructions
+// against about 35 of expm1f, and no further from fp64 (both 0.5-0.7 ulp at
+// worst over a grid of the range).
+__device__ __forceinline__ float expm1_near0(float x) {
+  float p = 1.0f / 40320.0f;
+  p = fmaf(p, x, 1.0f / 5040.0f);
+  p = fmaf(p, x, 1.0f / 720.0f);
+  p = fmaf(p, x, 1.0f / 120.0f);
+  p = fmaf(p, x, 1.0f / 24.0f);
+  p = fmaf(p, x, 1.0f / 6.0f);
+  p = fmaf(p, x, 0.5f);
+  return fmaf(x * x, p, x);
+}
+
+// One workgroup owns U runs of kSlotsPerBlock slots.  Indices fit 32 bits
+// (fewer than 2^31 slots; unsigned sums of a run stay below 2^32).
+template <int U>
 __global__ __launch_bounds__(kThreads) void grpo_kernel(const GrpoArgs a, int p2) {
-  __shared__ float adv_lds[kMaxResp];
+  constexpr uint32_t kRun = U * kSlotsPerBlock;
+  __shared__ float adv_lds[kRun + 2];  // responses overlapping the runs (T >= 1)
   __shared__ uint32_t red[kThreads / kWave];
 
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1);
   const int wave = tid / kWave;
-  const int64_t R = (int64_t)a.P * a.G;
+  const uint32_t R = (uint32_t)a.P * (uint32_t)a.G;
   const bool no_tokens = a.T == 0;
-  const int64_t T = no_tokens ? 1 : a.T;  // with T == 0 a run covers responses
-  const int64_t n_slots = R * T;
-  const int64_t c0 = (int64_t)blockIdx.x * kSlotsPerBlock;
-  const int64_t c1 = c0 + kSlotsPerBlock < n_slots ? c0 + kSlotsPerBlock : n_slots;
-  const int64_t j_lo = c0 / T;
-  const int64_t j_hi = (c1 - 1) / T;  // inclusive
-  const int64_t g_lo = j_lo / a.G;
-  const int64_t g_hi = j_hi / a.G;
+  const uint32_t T = no_tokens ? 1u : (uint32_t)a.T;  // with T == 0 a run covers responses
+  const uint32_t n_slots = R * T;
+  const uint32_t c0 = blockIdx.x * kRun;
+  const uint32_t c1 = c0 + kRun < n_slots ? c0 + kRun : n_slots;
+  const uint32_t j_lo = c0 / T;
+  const uint32_t j_hi = (c1 - 1) / T;  // inclusive
+  const uint32_t g_lo = j_lo / (uint32_t)a.G;
+  const uint32_t g_hi = j_hi / (uint32_t)a.G;
 
   // ---- loads first ----
   // Nothing below changes what a thread reads, so its token slots and the
   // first batch of mask words for the count are requested before any
   // arithmetic: the whole prologue then waits on memory about once.
-  const int i0 = (int)c0 + tid * kSlotsPerThread;  // P*G*T < 2^31
-  const bool has_slots = !no_tokens && i0 < c1;
-  float sn[4] = {0.f, 0.f, 0.f, 0.f}, so[4] = {0.f, 0.f, 0.f, 0.f}, sref[4] = {0.f, 0.f, 0.f, 0.f};
-  uint32_t mk = 0x01010101u;
-  const bool full = i0 + kSlotsPerThread <= c1;
-  if (has_slots) {
-    if (full) {
+  float sn[U][4], so[U][4], sref[U][4];
+  uint32_t mk[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const uint32_t i0 = c0 + (uint32_t)(u * kSlotsPerBlock + tid * kSlotsPerThread);
+    mk[u] = 0x01010101u;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) sn[u][k] = so[u][k] = sref[u][k] = 0.f;
+    if (no_tokens || i0 >= c1) continue;
+    if (i0 + kSlotsPerThread <= c1) {
       const float4 n4 = *reinterpret_cast<const float4 *>(a.logp_new + i0);
       const float4 o4 = *reinterpret_cast<const float4 *>(a.logp_old + i0);
-      sn[0] = n4.x; sn[1] = n4.y; sn[2] = n4.z; sn[3] = n4.w;
-      so[0] = o4.x; so[1] = o4.y; so[2] = o4.z; so[3] = o4.w;
+      sn[u][0] = n4.x; sn[u][1] = n4.y; sn[u][2] = n4.z; sn[u][3] = n4.w;
+      so[u][0] = o4.x; so[u][1] = o4.y; so[u][2] = o4.z; so[u][3] = o4.w;
       if (a.beta != 0.0f) {
         const float4 r4 = *reinterpret_cast<const float4 *>(a.logp_ref + i0);
-        sref[0] = r4.x; sref[1] = r4.y; sref[2] = r4.z; sref[3] = r4.w;
+        sref[u][0] = r4.x; sref[u][1] = r4.y; sref[u][2] = r4.z; sref[u][3] = r4.w;
       }
-      if (a.mask) mk = *reinterpret_cast<const uint32_t *>(a.mask + i0);
+      if (a.mask) mk[u] = *reinterpret_cast<const uint32_t *>(a.mask + i0);
     } else {
-      mk = 0;
+      mk[u] = 0;
+#pragma unroll
       for (int k = 0; k < kSlotsPerThread; ++k) {
-        const int i = i0 + k;
+        const uint32_t i = i0 + k;
         const bool in = i < c1;
-        sn[k] = in ? a.logp_new[i] : 0.0f;
-        so[k] = in ? a.logp_old[i] : 0.0f;
-        if (a.beta != 0.0f) sref[k] = in ? a.logp_ref[i] : 0.0f;
+        sn[u][k] = in ? a.logp_new[i] : 0.0f;
+        so[u][k] = in ? a.logp_old[i] : 0.0f;
+        if (a.beta != 0.0f) sref[u][k] = in ? a.logp_ref[i] : 0.0f;
         const uint32_t m = in ? (a.mask ? a.mask[i] : 1u) : 0u;
-        mk |= m << (8 * k);
+        mk[u] |= m << (8 * k);
       }
     }
   }
@@ -145,18 +175,20 @@ __global__ __launch_bounds__(kThreads) void grpo_kernel(const GrpoArgs a, int p2
   uint32_t pre = 0;
   if (!no_tokens && a.count_mask && a.counts && tid < a.n_counts) pre = a.counts[tid];
   const bool count_words = !no_tokens && a.count_mask && a.mask && !a.counts;
-  const int64_t n_words = count_words ? n_slots / 16 : 0;
+  const uint32_t n_words = count_words ? n_slots / 16 : 0;
   const uint4 *m4 = reinterpret_cast<const uint4 *>(a.mask);
   uint4 mw[kMaskBatch];
+  if constexpr (U == 1) {  // larger calls count in a pre-pass
 #pragma unroll
-  for (int u = 0; u < kMaskBatch; ++u) {
-    const int64_t i = (int64_t)u * kThreads + tid;
-    mw[u] = i < n_words ? m4[i] : make_uint4(0u, 0u, 0u, 0u);
+    for (int u = 0; u < kMaskBatch; ++u) {
+      const uint32_t i = (uint32_t)(u * kThreads + tid);
+      mw[u] = i < n_words ? m4[i] : make_uint4(0u, 0u, 0u, 0u);
+    }
   }
 
   // ---- advantages of the groups this run touches ----
-  for (int64_t grp = g_lo + wave; grp <= g_hi; grp += kThreads / kWave) {
-    const int64_t j = grp * a.G + lane;
+  for (uint32_t grp = g_lo + wave; grp <= g_hi; grp += kThreads / kWave) {
+    const uint32_t j = grp * (uint32_t)a.G + lane;
     const bool in = lane < a.G;
     const float rew = in ? a.rewards[j] : 0.0f;
     const float mu = group_sum(rew, p2) / (float)a.G;
@@ -178,22 +210,24 @@ __global__ __launch_bounds__(kThreads) void grpo_kernel(const GrpoArgs a, int p2
     if (a.counts) {
       cnt = pre;
     } else if (a.mask) {
-      for (int64_t base = 0; base < n_words; base += kMaskBatch * kThreads) {
-        if (base > 0) {  // later batches: all loads of a batch in flight at once
+      if constexpr (U == 1) {
+        for (uint32_t base = 0; base < n_words; base += kMaskBatch * kThreads) {
+          if (base > 0) {  // later batches: all loads of a batch in flight at once
 #pragma unroll
-          for (int u = 0; u < kMaskBatch; ++u) {
-            const int64_t i = base + (int64_t)u * kThreads + tid;
-            mw[u] = i < n_words ? m4[i] : make_uint4(0u, 0u, 0u, 0u);
+            for (int u = 0; u < kMaskBatch; ++u) {
+              const uint32_t i = base + (uint32_t)(u * kThreads + tid);
+              mw[u] = i < n_words ? m4[i] : make_uint4(0u, 0u, 0u, 0u);
+            }
           }
-        }
 #pragma unroll
-        for (int u = 0; u < kMaskBatch; ++u)
-          cnt += nonzero_bytes(mw[u].x) + nonzero_bytes(mw[u].y) + nonzero_bytes(mw[u].z) +
-                 nonzero_bytes(mw[u].w);
+          for (int u = 0; u < kMaskBatch; ++u)
+            cnt += nonzero_bytes(mw[u].x) + nonzero_bytes(mw[u].y) + nonzero_bytes(mw[u].z) +
+                   nonzero_bytes(mw[u].w);
+        }
+        for (uint32_t i = n_words * 16 + tid; i < n_slots; i += kThreads) cnt += a.mask[i] != 0;
       }
-      for (int64_t i = n_words * 16 + tid; i < n_slots; i += kThreads) cnt += a.mask[i] != 0;
     } else {
-      cnt = tid == 0 ? (uint32_t)n_slots : 0u;
+      cnt = tid == 0 ? n_slots : 0u;
     }
     for (int off = 1; off < kWave; off <<= 1) cnt += __shfl_xor(cnt, off, kWave);
     if (lane == 0) red[wave] = cnt;
@@ -205,36 +239,61 @@ __global__ __launch_bounds__(kThreads) void grpo_kernel(const GrpoArgs a, int p2
   }
 
   // ---- per-token quantities ----
-  if (!has_slots) return;
-
-  float rat[4], om[4];
-  uint32_t fl = 0;
 #pragma unroll
-  for (int k = 0; k < kSlotsPerThread; ++k) {
-    const int j = (i0 + k) / (int)T;
-    const float A = adv_lds[(j < j_hi ? j : j_hi) - j_lo];
-    const bool m = ((mk >> (8 * k)) & 0xFFu) != 0;
-    const float delta = sn[k] - so[k];
-    const bool chi = A >= 0.0f ? delta <= a.hi : delta >= a.lo;
-    const float r = expf(delta);
-    const float pol = chi ? r * A : 0.0f;
-    const float kl = a.beta != 0.0f ? a.beta * expm1f(sref[k] - sn[k]) : 0.0f;
-    rat[k] = r;
-    om[k] = m ? (-pol - kl) * inv_n : 0.0f;
-    const uint32_t f = (m && chi ? 1u : 0u) | (m && A != 0.0f && !chi ? 2u : 0u);
-    fl |= f << (8 * k);
-  }
-  if (full) {
-    *reinterpret_cast<float4 *>(a.coeff + i0) = make_float4(om[0], om[1], om[2], om[3]);
-    if (a.ratio) *reinterpret_cast<float4 *>(a.ratio + i0) = make_float4(rat[0], rat[1], rat[2], rat[3]);
-    *reinterpret_cast<uint32_t *>(a.flags + i0) = fl;
-  } else {
+  for (int u = 0; u < U; ++u) {
+    const uint32_t i0 = c0 + (uint32_t)(u * kSlotsPerBlock + tid * kSlotsPerThread);
+    if (i0 >= c1) continue;
+    float kl[4] = {0.f, 0.f, 0.f, 0.f};
+    if (a.beta != 0.0f) {
+      float d[4];
+      bool near0 = true;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        d[k] = sref[u][k] - sn[u][k];
+        near0 = near0 && fabsf(d[k]) <= 0.5f;
+      }
+      if (__all(near0)) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) kl[k] = a.beta * expm1_near0(d[k]);
+      } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) kl[k] = a.beta * expm1f(d[k]);
+      }
+    }
+    float rat[4], om[4];
+    uint32_t fl = 0;
+    uint32_t j = i0 / T, next = (j + 1) * T;  // response of slot i0, first slot of the next one
+#pragma unroll
     for (int k = 0; k < kSlotsPerThread; ++k) {
-      const int i = i0 + k;
-      if (i < c1) {
-        a.coeff[i] = om[k];
-        if (a.ratio) a.ratio[i] = rat[k];
-        a.flags[i] = (uint8_t)(fl >> (8 * k));
+      if (i0 + k == next) {
+        ++j;
+        next += T;
+      }
+      const float A = adv_lds[(j < j_hi ? j : j_hi) - j_lo];
+      const bool m = ((mk[u] >> (8 * k)) & 0xFFu) != 0;
+      const float delta = sn[u][k] - so[u][k];
+      const bool chi = A >= 0.0f ? delta <= a.hi : delta >= a.lo;
+      const float r = expf(delta);
+      const float pol = chi ? r * A : 0.0f;
+      rat[k] = r;
+      om[k] = m ? (-pol - kl[k]) * inv_n : 0.0f;
+      const uint32_t f = (m && chi ? 1u : 0u) | (m && A != 0.0f && !chi ? 2u : 0u);
+      fl |= f << (8 * k);
+    }
+    if (i0 + kSlotsPerThread <= c1) {
+      *reinterpret_cast<float4 *>(a.coeff + i0) = make_float4(om[0], om[1], om[2], om[3]);
+      if (a.ratio)
+        *reinterpret_cast<float4 *>(a.ratio + i0) = make_float4(rat[0], rat[1], rat[2], rat[3]);
+      *reinterpret_cast<uint32_t *>(a.flags + i0) = fl;
+    } else {
+#pragma unroll
+      for (int k = 0; k < kSlotsPerThread; ++k) {
+        const uint32_t i = i0 + k;
+        if (i < c1) {
+          a.coeff[i] = om[k];
+          if (a.ratio) a.ratio[i] = rat[k];
+          a.flags[i] = (uint8_t)(fl >> (8 * k));
+        }
       }
     }
   }
@@ -262,7 +321,7 @@ hipError_t launch_grpo(const GrpoArgs &a, uint32_t *counts, hipStream_t s) {
     if (nb > 0) {  // counted by a pre-pass into the workspace
       const int64_t n_words = slots / 16;
       const int64_t per = (n_words + nb - 1) / nb;
-      hipLaunchKernelGGL(count_kernel, dim3((unsigned)nb), dim3(kThreads), 0, s, a.mask, slots,
+      hipLaunchKernelGGL(count_kernel, dim3((unsigned)nb), dim3(kCountThreads), 0, s, a.mask, slots,
                          per, counts);
       const hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
@@ -270,8 +329,13 @@ hipError_t launch_grpo(const GrpoArgs &a, uint32_t *counts, hipStream_t s) {
       b.n_counts = nb;
     }
   }
-  const int64_t grid = (slots + kSlotsPerBlock - 1) / kSlotsPerBlock;
-  hipLaunchKernelGGL(grpo_kernel, dim3((unsigned)grid), dim3(kThreads), 0, s, b, p2);
+  // two runs per workgroup need the pre-pass (or no count), and the chip full
+  // with half the workgroups: at 2^20 slots 512 of them
+  const bool two = slots >= kTwoRunSlots && (b.counts || !a.mask || !a.count_mask);
+  const int64_t run = kSlotsPerBlock * (two ? 2 : 1);
+  const dim3 grid((unsigned)((slots + run - 1) / run));
+  if (two) hipLaunchKernelGGL(grpo_kernel<2>, grid, dim3(kThreads), 0, s, b, p2);
+  else hipLaunchKernelGGL(grpo_kernel<1>, grid, dim3(kThreads), 0, s, b, p2);
   return hipGetLastError();
 }
 
