@@ -11,10 +11,15 @@
 //             Prop. 1)
 //
 // Each workgroup of grpo_kernel owns a run of 1024 consecutive token slots
-// (4 per thread, 128-bit loads).  It first forms, with wave butterflies, the
-// advantages of every group its slots touch (a group of G <= 64 rewards sits
-// in the lanes of one wave; the group sums are the pairwise tree over the
-// next power of two >= G, which the xor butterfly produces exactly) and keeps
+// (4 per thread, 128-bit loads), from 2^20 slots on two runs (the group
+// statistics, the count and the launch ramp are then paid half as often; four
+// runs leave too few loads in flight).  At 2^22 masked slots with K3 and N
+// counted, in a graph: 28.3 us with one run, 64-bit indices, a division per slot
+// and expm1f throughout (then bound by its vector instructions), 19.4 us now, 23.0
+// with four runs; 92 MB at the copy rate take 15.  It first forms, with wave
+// butterflies, the advantages of every group its slots touch (a group of G <= 64
+// rewards sits in the lanes of one wave; the group sums are the pairwise tree over
+// the next power of two >= G, which the xor butterfly produces exactly) and keeps
 // them in LDS; then every thread processes its 4 slots elementwise.
 // When N has to be counted (no N given, a mask present), calls of at most
 // kGrpoCountInKernelSlots slots let every workgroup count the whole mask
@@ -99,8 +104,8 @@ __global__ __launch_bounds__(kCountThreads) void count_kernel(const uint8_t *mas
 
 // expm1 for |x| <= 1/2: the Taylor polynomial to x^8 (its remainder is below
 // 2^-26 of x there) closed by one rounding of x + x^2 P(x); 9 instructions
-// against about 35 of expm1f, and no further from fp64 (both 0.5-0.7 ulp at
-// worst over a grid of the range).
+// against about 35 of expm1f, and closer to fp64 (4e6 points of the range: 0.85
+// ulp at worst and 2.6e-8 rms, expm1f 1.37 and 2.9e-8).
 __device__ __forceinline__ float expm1_near0(float x) {
   float p = 1.0f / 40320.0f;
   p = fmaf(p, x, 1.0f / 5040.0f);
@@ -110,6 +115,16 @@ __device__ __forceinline__ float expm1_near0(float x) {
   p = fmaf(p, x, 1.0f / 6.0f);
   p = fmaf(p, x, 0.5f);
   return fmaf(x * x, p, x);
+}
+
+// Outputs of large calls (U > 1) stream past the caches, which leaves more of
+// them to the inputs: 2^22 slots 21.7 -> 19.3 us, 2^24 76 -> 72 us (inputs
+// loaded non-temporally too: 21.9 and 69).
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+template <int U, typename T, typename V>
+__device__ __forceinline__ void store(T *p, V v) {
+  if constexpr (U > 1) __builtin_nontemporal_store(v, reinterpret_cast<V *>(p));
+  else *reinterpret_cast<V *>(p) = v;
 }
 
 // One workgroup owns U runs of kSlotsPerBlock slots.  Indices fit 32 bits
@@ -245,20 +260,23 @@ __global__ __launch_bounds__(kThreads) void grpo_kernel(const GrpoArgs a, int p2
     if (i0 >= c1) continue;
     float kl[4] = {0.f, 0.f, 0.f, 0.f};
     if (a.beta != 0.0f) {
-      float d[4];
+      float d[4], e[4];
       bool near0 = true;
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         d[k] = sref[u][k] - sn[u][k];
+        e[k] = expm1_near0(d[k]);
         near0 = near0 && fabsf(d[k]) <= 0.5f;
       }
-      if (__all(near0)) {
+      if (!__all(near0)) {  // a slot's value depends on its own difference alone
 #pragma unroll
-        for (int k = 0; k < 4; ++k) kl[k] = a.beta * expm1_near0(d[k]);
-      } else {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) kl[k] = a.beta * expm1f(d[k]);
+        for (int k = 0; k < 4; ++k) {
+          const float far = expm1f(d[k]);
+          e[k] = fabsf(d[k]) <= 0.5f ? e[k] : far;
+        }
       }
+#pragma unroll
+      for (int k = 0; k < 4; ++k) kl[k] = a.beta * e[k];
     }
     float rat[4], om[4];
     uint32_t fl = 0;
@@ -281,10 +299,9 @@ __global__ __launch_bounds__(kThreads) void grpo_kernel(const GrpoArgs a, int p2
       fl |= f << (8 * k);
     }
     if (i0 + kSlotsPerThread <= c1) {
-      *reinterpret_cast<float4 *>(a.coeff + i0) = make_float4(om[0], om[1], om[2], om[3]);
-      if (a.ratio)
-        *reinterpret_cast<float4 *>(a.ratio + i0) = make_float4(rat[0], rat[1], rat[2], rat[3]);
-      *reinterpret_cast<uint32_t *>(a.flags + i0) = fl;
+      store<U>(a.coeff + i0, f32x4{om[0], om[1], om[2], om[3]});
+      if (a.ratio) store<U>(a.ratio + i0, f32x4{rat[0], rat[1], rat[2], rat[3]});
+      store<U>(a.flags + i0, fl);
     } else {
 #pragma unroll
       for (int k = 0; k < kSlotsPerThread; ++k) {
