@@ -11,19 +11,20 @@
 //   F_i(j, k) = max over available a of F_{i-1}(j - b_i(a), k - r_i(a)) + tau_i(a)
 // runs over the (N_B + 1) x (N_delta + 1) grid of exact integer costs.
 //
-// Mapping.  One launch per pair of units updates the whole grid, one thread
-// per cell (rows k of risk cost, columns j of memory cost, a row padded to a
-// multiple of 64 cells so that a wave covers 64 consecutive cells of one row;
-// each XCD takes one contiguous band of cells).  Each cell forms the first
-// unit's value at itself and at the two cells the second unit's actions
-// shift it to, from up to nine cells of the table before the pair (fp64, all
-// in the 256 MB infinity cache for grids up to a few thousand squared), and
-// writes the value after the pair; the chosen action (2 bits) of each unit is
-// gathered across the wave with two ballots and stored as two 64-bit masks
-// per 64 cells, so the backtracking record of a 1025 x 1025 grid is 279 KB
-// per unit.  A reduction kernel then finds the best terminal cell, one wave
-// backtracks through the records (four units per round trip), and one wave
-// sums the chosen costs in unit order.
+// Mapping.  One launch (setup_kernel) forms the integer costs, the memory cost
+// reach after each unit and the initial tables.  Then one launch per pair of
+// units updates the whole grid, one thread per cell (rows k of risk cost,
+// columns j of memory cost, a row padded to a multiple of 64 cells so that a wave
+// covers 64 consecutive cells of one row; each XCD takes one contiguous band of
+// cells: 734 -> 834 us for 196 units without).  Each cell forms the first unit's
+// value at itself and at the two cells the second unit's actions shift it to,
+// from up to nine cells of the table before the pair (fp64, all in the 256 MB
+// infinity cache for grids up to a few thousand squared), and writes the value
+// after the pair; the chosen actions come out of the comparisons as lane masks
+// and are stored as two 64-bit words per unit and 64 cells, so the backtracking
+// record of a 1025 x 1025 grid is 279 KB per unit.  A reduction kernel then finds
+// the best terminal cell, and one wave backtracks through the records (four units
+// per round trip) and sums the chosen costs in unit order.
 //
 // Every value is produced by the same fp64 operations in the same order as
 // a plain sequential implementation (one addition per unit along a path,
@@ -39,13 +40,13 @@ namespace hilore {
 namespace {
 
 constexpr int kActR = 0, kActH = 1, kActL = 2;
+typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
 constexpr int kDpThreads = 256;
 constexpr int kPartials = 1024;  // workgroups of the terminal reduction
 constexpr int kFinalThreads = 1024;
-#ifndef HILORE_DP_GROUP
-#define HILORE_DP_GROUP 2
-#endif
-constexpr int kDpGroup = HILORE_DP_GROUP;  // units per DP launch (1 .. 4)
+constexpr int kDpGroup = 2;  // units per DP launch
+
+constexpr int kNever = 1 << 20;  // risk cost of an unavailable action: no state can pay it
 
 // Availability of a non-R action (App. B.3 Eq. available-recovery-actions;
 // non-R actions with non-positive utility are excluded, App. B.2): verified,
@@ -72,178 +73,180 @@ __device__ int64_t grid_cost(double cost, double budget, int n) {
   return c > (double)n ? (int64_t)n + 1 : (int64_t)c;
 }
 
-__global__ void costs_kernel(const AllocArgs a, AllocUnitCost *uc) {
-  const int u = blockIdx.x * blockDim.x + threadIdx.x;
-  if (u >= a.U) return;
+__device__ AllocUnitCost unit_cost(const AllocArgs &a, int u) {
   const uint8_t q = a.q[u], v = a.verified[u];
-  int ok_h = action_ok(kActH, q, v, a.tau_h[u], a.dm_h[u], 0.0);
-  int ok_l = action_ok(kActL, q, v, a.tau_l[u], a.dm_l[u], a.psi[u]) && a.delta_b > 0.0;
-  const int64_t b_h = ok_h ? grid_cost(a.dm_h[u], a.m_res, a.n_b) : 0;
-  const int64_t b_l = ok_l ? grid_cost(a.dm_l[u], a.m_res, a.n_b) : 0;
-  const int64_t r_l = ok_l ? grid_cost(a.psi[u], a.delta_b, a.n_d) : 0;
+  const double tau_h = a.tau_h[u], tau_l = a.tau_l[u], dm_h = a.dm_h[u], dm_l = a.dm_l[u];
+  const double psi = a.psi[u];
+  int ok_h = action_ok(kActH, q, v, tau_h, dm_h, 0.0);
+  int ok_l = action_ok(kActL, q, v, tau_l, dm_l, psi) && a.delta_b > 0.0;
+  const int64_t b_h = ok_h ? grid_cost(dm_h, a.m_res, a.n_b) : 0;
+  const int64_t b_l = ok_l ? grid_cost(dm_l, a.m_res, a.n_b) : 0;
+  const int64_t r_l = ok_l ? grid_cost(psi, a.delta_b, a.n_d) : 0;
   if (b_h > a.n_b) ok_h = 0;
   if (b_l > a.n_b || r_l > a.n_d) ok_l = 0;
   AllocUnitCost c;
-  c.ok_h = ok_h;
-  c.ok_l = ok_l;
-  c.b_h = (int32_t)b_h;
-  c.b_l = (int32_t)b_l;
-  c.r_l = (int32_t)r_l;
-  c.reach = 0;  // set by reach_kernel
-  c.tau_h = a.tau_h[u];
-  c.tau_l = a.tau_l[u];
-  uc[u] = c;
+  c.b_h = ok_h ? (int32_t)b_h : 0;
+  c.r_h = ok_h ? 0 : kNever;
+  c.b_l = ok_l ? (int32_t)b_l : 0;
+  c.r_l = ok_l ? (int32_t)r_l : kNever;
+  c.reach = 0;
+  c.tau_h = tau_h;
+  c.tau_l = tau_l;
+  return c;
 }
 
-// Memory cost reach after each unit: the running sum, in unit order, of the
-// largest memory cost of each unit's available actions, capped at KB - 1
-// (integers, one workgroup: a scan per chunk of 1024 units plus a carry).
-// No state after unit i has a memory cost above uc[i].reach.
-constexpr int kReachThreads = 1024;
-__global__ __launch_bounds__(kReachThreads) void reach_kernel(AllocUnitCost *uc, int U, int KB) {
-  __shared__ int part[kReachThreads];
+// Before the DP, in one launch.  Workgroup 0: the integer costs of every unit
+// and the memory cost reach after it, i.e. the running sum, in unit order, of
+// the largest memory cost of each unit's available actions, capped at KB - 1
+// (a scan per chunk of 1024 units plus a carry): no state after unit i has a
+// memory cost above uc[i].reach.  The other workgroups: F_0, which is 0 at
+// (0, 0) and -inf elsewhere (padding cells included), and the second table all
+// -inf (a DP launch skips the waves whose cells lie beyond the reach, which must
+// then read as unreachable in either table); the guard cell holds -inf.
+constexpr int kSetupThreads = 1024;
+constexpr int kSetupCells = 4 * kSetupThreads;  // cells of each table per workgroup
+__global__ __launch_bounds__(kSetupThreads) void setup_kernel(const AllocArgs a, AllocUnitCost *uc,
+                                                              int KB, double *f0, double *f1,
+                                                              int64_t cells, double *guard) {
+  __shared__ int part[kSetupThreads];
   const int tid = (int)threadIdx.x;
-  int carry = 0;
-  for (int base = 0; base < U; base += kReachThreads) {
-    const int i = base + tid;
-    int v = 0;
-    if (i < U) {
-      const AllocUnitCost c = uc[i];
-      v = max(c.ok_h ? c.b_h : 0, c.ok_l ? c.b_l : 0);  // each at most KB
+  if (blockIdx.x > 0) {
+    const int64_t c0 = (int64_t)(blockIdx.x - 1) * kSetupCells + tid;
+#pragma unroll
+    for (int i = 0; i < kSetupCells / kSetupThreads; ++i) {
+      const int64_t cell = c0 + i * kSetupThreads;
+      if (cell < cells) {
+        f0[cell] = cell == 0 ? 0.0 : -INFINITY;
+        f1[cell] = -INFINITY;
+      }
     }
+    return;
+  }
+  if (tid == 0) *guard = -INFINITY;
+  int carry = 0;
+  for (int base = 0; base < a.U; base += kSetupThreads) {
+    const int i = base + tid;
+    AllocUnitCost c{};
+    if (i < a.U) c = unit_cost(a, i);
+    const int v = max(c.b_h, c.b_l);  // 0 for an action that is not available, each at most KB
     part[tid] = v;
     __syncthreads();
-    for (int off = 1; off < kReachThreads; off <<= 1) {
+    for (int off = 1; off < kSetupThreads; off <<= 1) {
       const int t = tid >= off ? part[tid - off] : 0;
       __syncthreads();
       part[tid] += t;  // at most 1024 * KB: no overflow for KB <= 4097
       __syncthreads();
     }
-    if (i < U) uc[i].reach = min(KB - 1, carry + part[tid]);
-    carry = min(KB, carry + part[kReachThreads - 1]);
+    c.reach = min(KB - 1, carry + part[tid]);
+    if (i < a.U) uc[i] = c;
+    carry = min(KB, carry + part[kSetupThreads - 1]);
     __syncthreads();
   }
 }
 
-// F_0: 0 at (0, 0), -inf elsewhere (padding cells included), and the second
-// table all -inf: a DP launch skips the waves whose cells lie beyond the
-// memory cost reach, which must then read as unreachable in either table.
-__global__ void init_kernel(double *f0, double *f1, int64_t cells) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < cells) {
-    f0[i] = i == 0 ? 0.0 : -INFINITY;
-    f1[i] = -INFINITY;
-  }
+// The larger of two values; a NaN (-inf plus the tau of an unavailable action,
+// which may be anything) loses.  No value here is a signalling NaN or -0.
+__device__ __forceinline__ double max_f64(double a, double b) {
+  double r;
+  asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
 }
 
-// F_i(j, k) of one unit of Eq. allocation-dp from the previous table: the
-// actions R, H, L in this order, each replacing the incumbent only when
-// strictly larger (the within-state tie rule); `act` receives the chosen
-// action.  The caller guarantees 0 <= j < KB and 0 <= k; padding cells
-// (j >= KB) stay -inf.
-__device__ __forceinline__ double unit_value(const double *__restrict__ prev,
-                                             const AllocUnitCost &c, int64_t cell, int j, int k,
-                                             int S, int &act) {
-  double best = prev[cell];
-  act = kActR;
-  if (c.ok_h && c.b_h <= j) {
-    const double v = prev[cell - c.b_h] + c.tau_h;
-    if (v > best) {
-      best = v;
-      act = kActH;
-    }
-  }
-  if (c.ok_l && c.b_l <= j && c.r_l <= k) {
-    const double v = prev[cell - (int64_t)c.r_l * S - c.b_l] + c.tau_l;
-    if (v > best) {
-      best = v;
-      act = kActL;
-    }
-  }
-  return best;
-}
+constexpr int ipow3(int n) { return n == 0 ? 1 : 3 * ipow3(n - 1); }
 
-// F after the units c[0 .. N-1] (applied in order to the table `prev`) at
-// cell (j, k), by the rule of Eq. allocation-dp for the last unit applied to
-// the values after the first N - 1 at the cells its actions shift (j, k) to,
-// down to unit_value on `prev`.  Every value is formed by the same fp64
-// additions and comparisons, in the same order, as N single-unit launches
-// would form it.  With `acts`, acts[m] receives unit m's action at (j, k)
-// itself (the chain through the unshifted cell), i.e. its record there.
+// F after the N consecutive units uc[0 .. N-1] from the table before them, and
+// the records of all N: bit for bit what N single-unit launches would write
+// (every value is formed by the same fp64 additions and comparisons in the same
+// order: actions R, H, L, each replacing the incumbent only when strictly
+// larger); the tables in between are never stored.  One thread per cell; a cell
+// combines up to 3^N cells of the table before, one per choice of actions
+// ("source"), each the same shift for the whole wave, so a source that no action
+// or no row can provide costs a scalar branch.  All loads are requested before
+// any is used.
+// What bounds a launch is the round trip of the table through the memory behind
+// the L2s (17.8 MB, cold in every launch) on top of the launch itself: 6.3 us a
+// pair of units on the 1025 x 1025 grid, of which 2.8 are left on a grid a
+// sixteenth of it.  With a 64-bit division, a branch and a wait per source the
+// chain of dependent loads came on top (7.2 us).  Measured and not better: 3
+// units a launch (27 sources: 758 against 683 us for 196 units; better only on
+// small grids), one unit (1004), 2, 3 or 6 chunks a wave (883 to 1211: longer
+// code, fetched cold by every launch), workgroups of 128 and 1024 threads.
 template <int N>
-__device__ __forceinline__ double chain_value(const double *__restrict__ prev,
-                                              const AllocUnitCost *c, int64_t cell, int j, int k,
-                                              int S, int *acts) {
-  if constexpr (N == 1) {
-    int a;
-    const double v = unit_value(prev, c[0], cell, j, k, S, a);
-    if (acts) acts[0] = a;
-    return v;
-  } else {
-    double best = chain_value<N - 1>(prev, c, cell, j, k, S, acts);
-    int act = kActR;
-    const AllocUnitCost &u = c[N - 1];
-    if (u.ok_h && u.b_h <= j) {
-      const double v =
-          chain_value<N - 1>(prev, c, cell - u.b_h, j - u.b_h, k, S, nullptr) + u.tau_h;
-      if (v > best) {
-        best = v;
-        act = kActH;
-      }
-    }
-    if (u.ok_l && u.b_l <= j && u.r_l <= k) {
-      const double v = chain_value<N - 1>(prev, c, cell - (int64_t)u.r_l * S - u.b_l,
-                                          j - u.b_l, k - u.r_l, S, nullptr) +
-                       u.tau_l;
-      if (v > best) {
-        best = v;
-        act = kActL;
-      }
-    }
-    if (acts) acts[N - 1] = act;
-    return best;
-  }
-}
-
-// N consecutive units of Eq. allocation-dp in one launch: each cell reads up
-// to 3^N cells of the table before the group (the shifted ones mostly from
-// the cache) and writes the table after it and the records of all N units,
-// bit for bit what N launches of one unit each would write; the tables in
-// between are never stored.
-template <int N>
-__global__ __launch_bounds__(kDpThreads) void dpn_kernel(const double *__restrict__ prev,
-                                                          double *__restrict__ cur,
-                                                          uint64_t *__restrict__ pred,
-                                                          size_t pred_words_per_unit,
-                                                          const AllocUnitCost *__restrict__ uc,
-                                                          int KB, int KD, int S) {
-  const int n = (int)gridDim.x, x = (int)blockIdx.x & 7, q = n >> 3, rem = n & 7;
-  const int bid = x * q + (x < rem ? x : rem) + ((int)blockIdx.x >> 3);
-  const int64_t cell = (int64_t)bid * kDpThreads + threadIdx.x;
-  const int k = (int)(cell / S), j = (int)(cell % S);
-  if (k >= KD) return;  // whole waves: S and the grid are multiples of 64
+__global__ __launch_bounds__(kDpThreads) void dpn_kernel(
+    const double *__restrict__ prev, double *__restrict__ cur, uint64_t *__restrict__ pred,
+    const AllocUnitCost *__restrict__ uc, uint32_t pred_words_per_unit, uint32_t chunks,
+    uint32_t chunk_recip, uint32_t n, int KB, int KD, uint32_t guard) {
+  const uint32_t x = blockIdx.x & 7u, q = n >> 3, rem = n & 7u;
+  const uint32_t bid = x * q + (x < rem ? x : rem) + (blockIdx.x >> 3);
+  const int lane = (int)threadIdx.x & (kWave - 1);
+  // this wave's 64-cell chunk, its row k and first column j0
+  const uint32_t w = bid * (kDpThreads / kWave) +
+                     (uint32_t)__builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+  const int k = (int)(chunks == 1 ? w : __umulhi(w, chunk_recip));
+  const int j0 = (int)(w - (uint32_t)k * chunks) * kWave;
   AllocUnitCost c[N];
 #pragma unroll
-  for (int m = 0; m < N; ++m) c[m] = uc[m];
+  for (int m = 0; m < N; ++m) {
+    c[m] = uc[m];
+    // all of it now, not behind the branches below
+    asm volatile("" ::"s"(c[m].b_h), "s"(c[m].r_h), "s"(c[m].b_l), "s"(c[m].r_l),
+                 "s"(c[m].reach), "s"(c[m].tau_h), "s"(c[m].tau_l));
+  }
+  if (k >= KD) return;
   // A wave (64 consecutive cells of one row) wholly beyond the memory cost
   // reach after the group holds only unreachable states: they stay -inf in
   // both tables, and no path the backtrack follows passes through them, so
   // neither their values nor their records are written.
-  if (__builtin_amdgcn_readfirstlane(j) > c[N - 1].reach) return;
-  int acts[N];
+  if (j0 > c[N - 1].reach) return;
+  const int j = j0 + lane < KB ? j0 + lane : -1;  // padding cells: nothing leads here
+  const uint32_t cell8 = (w * kWave + (uint32_t)lane) * 8u;  // byte offset of this cell
+
+  // source s: unit m takes action (s / 3^m) % 3; a lane without it reads the
+  // guard cell, which holds -inf
+  constexpr int kSrc = ipow3(N);
+  const __amdgpu_buffer_rsrc_t table = __builtin_amdgcn_make_buffer_rsrc(
+      (void *)prev, 0, (int)(guard + 8u), 0x00020000);
+  double none = -INFINITY;
+  asm("" : "+s"(none));
+  double f[kSrc];
 #pragma unroll
-  for (int m = 0; m < N; ++m) acts[m] = kActR;
-  double best = -INFINITY;
-  if (j < KB) best = chain_value<N>(prev, c, cell, j, k, S, acts);
-  cur[cell] = best;
-  const int64_t w = cell / kWave;  // 64-cell chunk of this wave
+  for (int s = 0; s < kSrc; ++s) {
+    int db = 0, dk = 0;
 #pragma unroll
-  for (int m = 0; m < N; ++m) {
-    const uint64_t lo = __ballot(acts[m] & 1), hi = __ballot(acts[m] >> 1);
-    if ((threadIdx.x & (kWave - 1)) == 0) {
-      pred[m * pred_words_per_unit + 2 * w] = lo;
-      pred[m * pred_words_per_unit + 2 * w + 1] = hi;
+    for (int m = 0; m < N; ++m) {
+      const int act = s / ipow3(m) % 3;
+      if (act == kActH) db += c[m].b_h, dk += c[m].r_h;
+      if (act == kActL) db += c[m].b_l, dk += c[m].r_l;
     }
+    f[s] = none;
+    if (s == 0 || dk <= k) {  // the same for the whole wave
+      const uint32_t from = cell8 - ((uint32_t)dk * chunks * kWave + (uint32_t)db) * 8u;
+      f[s] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(
+                                            table, (int)(j >= db ? from : guard), 0, 0));
+    }
+  }
+  uint64_t lo[N], hi[N];  // records: bit 0 and 1 of the action, one bit per lane
+#pragma unroll
+  for (int m = 0; m < N; ++m)
+#pragma unroll
+    for (int t = 0; t < ipow3(N - 1 - m); ++t) {
+      const double r = f[3 * t];
+      const double vh = f[3 * t + 1] + c[m].tau_h, vl = f[3 * t + 2] + c[m].tau_l;
+      const double rh = max_f64(r, vh);
+      if (t == 0) {  // the record of the cell itself
+        hi[m] = __ballot(vl > rh);
+        lo[m] = __ballot(vh > r) & ~hi[m];
+      }
+      f[t] = max_f64(rh, vl);
+    }
+  // Written through at device scope: a table left dirty in the L2s is flushed at
+  // the launch's end, with every CU idle (731 -> 679 us for 196 units).
+  __hip_atomic_store(reinterpret_cast<double *>(reinterpret_cast<char *>(cur) + cell8), f[0],
+                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (lane == 0) {
+#pragma unroll
+    for (int m = 0; m < N; ++m)
+      *reinterpret_cast<u64x2 *>(pred + (m * pred_words_per_unit + 2u * w)) = u64x2{lo[m], hi[m]};
   }
 }
 
@@ -299,6 +302,55 @@ __device__ __forceinline__ int record(const uint64_t *pred, int64_t unit, int64_
 
 __device__ __forceinline__ int lane_int(int v, int lane) {
   return __builtin_amdgcn_readlane(v, lane);
+}
+
+__device__ __forceinline__ double lane_f64(double v, int lane) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, lane);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// Memory and risk of the chosen actions, summed in unit order (one wave:
+// the inputs of 64 units are loaded at once, one chunk ahead, and the
+// additions stay sequential).  A unit whose action adds nothing adds +0.0,
+// which leaves the sums unchanged: they start at +0.0 and every chosen cost
+// is finite and non-negative, so neither sum is ever -0.0.
+struct UnitTotals {
+  double mem, risk;
+};
+
+__device__ __forceinline__ UnitTotals unit_costs(const AllocArgs &a, int u) {
+  UnitTotals c{0.0, 0.0};
+  if (u < a.U) {
+    const int act = a.action[u];
+    if (act == kActH) c.mem = a.dm_h[u];
+    if (act == kActL) {
+      c.mem = a.dm_l[u];
+      c.risk = a.psi[u];
+    }
+  }
+  return c;
+}
+
+__device__ __forceinline__ void sum_chosen(const AllocArgs &a, int lane) {
+  double mem = 0.0, risk = 0.0;
+  UnitTotals c = unit_costs(a, lane);
+  for (int base = 0; base < a.U; base += kWave) {
+    const UnitTotals next = unit_costs(a, base + kWave + lane);
+    // all 64 lanes, unrolled (constant lane indices): lanes past the last
+    // unit hold +0.0, which leaves the sums unchanged
+#pragma unroll
+    for (int t = 0; t < kWave; ++t) {
+      mem += lane_f64(c.mem, t);
+      risk += lane_f64(c.risk, t);
+    }
+    c = next;
+  }
+  if (lane == 0) {
+    a.totals[1] = mem;
+    a.totals[2] = risk;
+  }
 }
 
 // Backtracking, one wave.  The record of unit i at the current cell decides
@@ -400,56 +452,8 @@ __global__ __launch_bounds__(kFinalThreads) void terminal_backtrack_kernel(
     bl = nbl;
     rl = nrl;
   }
-}
-
-__device__ __forceinline__ double lane_f64(double v, int lane) {
-  const uint64_t u = __builtin_bit_cast(uint64_t, v);
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, lane);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane);
-  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-
-// Memory and risk of the chosen actions, summed in unit order (one wave:
-// the inputs of 64 units are loaded at once, one chunk ahead, and the
-// additions stay sequential).  A unit whose action adds nothing adds +0.0,
-// which leaves the sums unchanged: they start at +0.0 and every chosen cost
-// is finite and non-negative, so neither sum is ever -0.0.
-struct UnitTotals {
-  double mem, risk;
-};
-
-__device__ __forceinline__ UnitTotals unit_costs(const AllocArgs &a, int u) {
-  UnitTotals c{0.0, 0.0};
-  if (u < a.U) {
-    const int act = a.action[u];
-    if (act == kActH) c.mem = a.dm_h[u];
-    if (act == kActL) {
-      c.mem = a.dm_l[u];
-      c.risk = a.psi[u];
-    }
-  }
-  return c;
-}
-
-__global__ __launch_bounds__(kWave) void totals_kernel(const AllocArgs a) {
-  const int lane = (int)threadIdx.x;
-  double mem = 0.0, risk = 0.0;
-  UnitTotals c = unit_costs(a, lane);
-  for (int base = 0; base < a.U; base += kWave) {
-    const UnitTotals next = unit_costs(a, base + kWave + lane);
-    // all 64 lanes, unrolled (constant lane indices): lanes past the last
-    // unit hold +0.0, which leaves the sums unchanged
-#pragma unroll
-    for (int t = 0; t < kWave; ++t) {
-      mem += lane_f64(c.mem, t);
-      risk += lane_f64(c.risk, t);
-    }
-    c = next;
-  }
-  if (lane == 0) {
-    a.totals[1] = mem;
-    a.totals[2] = risk;
-  }
+  __threadfence_block();  // the actions are read back by other lanes
+  sum_chosen(a, lane);
 }
 
 }  // namespace
@@ -478,38 +482,41 @@ hipError_t launch_allocate(const AllocArgs &a, int KB, int KD, void *workspace, 
   Best *partial = reinterpret_cast<Best *>(ws + l.off_partial);
   uint64_t *pred = reinterpret_cast<uint64_t *>(ws + l.off_pred);
 
-  if (a.U > 0) {
-    hipLaunchKernelGGL(costs_kernel, dim3((a.U + 255) / 256), dim3(256), 0, s, a, uc);
-    hipLaunchKernelGGL(reach_kernel, dim3(1), dim3(kReachThreads), 0, s, uc, a.U, KB);
-  }
+  const int setup_grid = 1 + (int)((l.cells + kSetupCells - 1) / kSetupCells);
+  hipLaunchKernelGGL(setup_kernel, dim3(setup_grid), dim3(kSetupThreads), 0, s, a, uc, KB, f[0],
+                     f[1], l.cells, reinterpret_cast<double *>(partial));
   const int grid = (int)((l.cells + kDpThreads - 1) / kDpThreads);
-  hipLaunchKernelGGL(init_kernel, dim3(grid), dim3(kDpThreads), 0, s, f[0], f[1], l.cells);
   auto pred_of = [&](int i) {
     return reinterpret_cast<uint64_t *>(reinterpret_cast<char *>(pred) +
                                         l.pred_bytes_per_unit * (size_t)i);
   };
   // units in groups of kDpGroup (one launch each), the rest in a smaller
   // group; the table after launch t lives in f[t & 1]
-  const size_t words = l.pred_bytes_per_unit / sizeof(uint64_t);
+  const uint32_t words = (uint32_t)(l.pred_bytes_per_unit / sizeof(uint64_t));
+  // w / chunks = mulhi(w, recip) for every chunk w of a table (at most 2^19 of
+  // them and 65 a row, so w < 2^32 / chunks)
+  const uint32_t chunks = (uint32_t)(l.S / kWave);
+  const uint32_t recip = (uint32_t)((uint64_t(1) << 32) / chunks + 1);
   int t = 0;
   for (int i = 0; i < a.U; i += kDpGroup, ++t) {
     const int g = a.U - i < kDpGroup ? a.U - i : kDpGroup;
     const dim3 gd(grid), bd(kDpThreads);
+    const uint32_t guard = (uint32_t)(l.off_partial - (t & 1 ? l.off_f1 : l.off_f0));
     double *src = f[t & 1], *dst = f[(t + 1) & 1];
     uint64_t *pr = pred_of(i);
-    switch (g) {
-      case 1: hipLaunchKernelGGL(dpn_kernel<1>, gd, bd, 0, s, src, dst, pr, words, uc + i, KB, KD, l.S); break;
-      case 2: hipLaunchKernelGGL(dpn_kernel<2>, gd, bd, 0, s, src, dst, pr, words, uc + i, KB, KD, l.S); break;
-      case 3: hipLaunchKernelGGL(dpn_kernel<3>, gd, bd, 0, s, src, dst, pr, words, uc + i, KB, KD, l.S); break;
-      default: hipLaunchKernelGGL(dpn_kernel<4>, gd, bd, 0, s, src, dst, pr, words, uc + i, KB, KD, l.S); break;
-    }
+    auto launch = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, gd, bd, 0, s, src, dst, pr, uc + i, words, chunks, recip,
+                         (uint32_t)grid, KB, KD, guard);
+    };
+    if (g == 1) launch(dpn_kernel<1>);
+    else if (g == 2) launch(dpn_kernel<2>);
+    else launch(dpn_kernel<3>);
   }
   const int n_partial = grid < kPartials ? grid : kPartials;
   hipLaunchKernelGGL(terminal_partial_kernel, dim3(n_partial), dim3(kDpThreads), 0, s,
                      f[t & 1], l.cells, partial);
   hipLaunchKernelGGL(terminal_backtrack_kernel, dim3(1), dim3(kFinalThreads), 0, s, a, partial,
                      n_partial, pred, uc, l.S, KD);
-  hipLaunchKernelGGL(totals_kernel, dim3(1), dim3(kWave), 0, s, a);
   return hipGetLastError();
 }
 

@@ -144,9 +144,9 @@ struct AllocArgs {
   double *totals;
   int64_t *jk;
 };
-struct AllocUnitCost {  // integer costs of one unit on the grid
-  int32_t ok_h, ok_l;
-  int32_t b_h, b_l, r_l;
+struct AllocUnitCost {  // integer costs of one unit on the grid: memory b, risk r
+  int32_t b_h, r_h;  // r_h is 0; an action that is not available has b = 0 and a risk
+  int32_t b_l, r_l;  // cost that no state can pay
   int32_t reach;  // largest memory cost of any state after this unit (cumulative, < KB)
   double tau_h, tau_l;
 };
