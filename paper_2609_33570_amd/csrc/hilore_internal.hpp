@@ -43,6 +43,7 @@ struct CodecBatch {
   int n;
   int stats;     // compress: write row sums
   int wpr_log2;  // log2 of the waves per row, 0..4
+  int rpw_log2;  // log2 of the rows per wave, 0..3; above 0 row_begin counts groups of rows
 };
 
 // Waves per row (as log2, 0..4) for rows of `cols` columns: the fewest that
@@ -57,6 +58,20 @@ inline int codec_wpr_log2(int64_t cols, int lane_steps) {
   int wl = 0;
   while (wl < 4 && (int64_t(64 * lane_steps) << wl) < steps) ++wl;
   return wl;
+}
+
+// Rows per wave (as log2) for narrow rows.  A wave issues four loads of 512
+// columns at once; a row of up to 1024 columns fills half of them or less, and
+// a wave that moves 1-3 KB and ends leaves the memory idle (16384 x 512 x 8
+// units: encode 62 us, decode 45, against 33 at the copy rate).  So a wave takes
+// 2, 4 or 8 such rows: as many as four loads hold, two rows to a load up to 256
+// columns.  Only in calls of enough rows that the chip stays full with fewer
+// waves, only whole 8-column pieces (rows of the literal cast may end anywhere),
+// and strides that keep a group's byte offsets in 32 bits.
+constexpr int64_t kGroupedRows = 8192;
+inline int codec_rpw_log2(int64_t cols, int64_t ld, int64_t call_rows) {
+  if (call_rows < kGroupedRows || cols % 8 != 0 || ld > (int64_t(1) << 24)) return 0;
+  return cols <= 256 ? 3 : cols <= 512 ? 2 : cols <= 1024 ? 1 : 0;
 }
 
 hipError_t launch_compress(const CodecBatch &b, int code, int block, hipStream_t s);
