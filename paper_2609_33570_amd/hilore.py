@@ -276,24 +276,37 @@ def hilore_wgrad_workspace_bytes(K: int, M: int, N: int) -> int:
     return int(load().hilore_wgrad_workspace_bytes(int(K), int(M), int(N)))
 
 
+def _wgrad_workspace(nbytes: int, device, stream):
+    """A buffer from torch's allocator in the order of the call's stream (an explicit
+    one has a pool of its own there, so the buffer's reuse follows that stream's work),
+    or None: no memory left, or an explicit stream under capture, whose graph would
+    keep using a buffer that the allocator gives to others."""
+    import torch
+
+    try:
+        if stream is None:
+            return torch.empty(nbytes, dtype=torch.uint8, device=device)
+        with torch.cuda.stream(torch.cuda.ExternalStream(int(stream), device=device)):
+            if torch.cuda.is_current_stream_capturing():
+                return None
+            return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    except torch.cuda.OutOfMemoryError:
+        return None
+
+
 def hilore_dequant_wgrad(x_codes, x_scales, code, block: int, dy, dw, K: int, M: int, N: int,
                          accumulate: bool = False, stream=None, workspace=None):
     """workspace: a device tensor of at least hilore_wgrad_workspace_bytes(K, M, N) bytes
     for the partial sums of split tiles.  None: a buffer of that size from torch's
-    allocator, or the unsplit call where that cannot be had (an explicit stream, no
-    memory left)."""
+    allocator, or the unsplit call where that cannot be had (no memory left, an explicit
+    stream under capture)."""
     L = load()
     args = (_p(x_codes), _p(x_scales), _code(code), int(block), _p(dy), _p(dw), int(K), int(M),
             int(N), 1 if accumulate else 0)
-    if workspace is None and stream is None:
+    if workspace is None:
         need = L.hilore_wgrad_workspace_bytes(args[6], args[7], args[8])
         if need:
-            import torch
-
-            try:
-                workspace = torch.empty(need, dtype=torch.uint8, device=dw.device)
-            except torch.cuda.OutOfMemoryError:
-                pass
+            workspace = _wgrad_workspace(need, dw.device, stream)
     if workspace is None:
         st = L.hilore_dequant_wgrad(*args, _stream(stream))
     else:

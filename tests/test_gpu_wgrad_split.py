@@ -67,17 +67,54 @@ def test_split_matches_unsplit(hl, code, block, K, M, N, accumulate):
     dw0 = (torch.randint(-50, 51, (M, N), generator=g, device="cuda").float() if accumulate
            else torch.full((M, N), float("nan"), device="cuda"))
     buf = torch.full((need + GUARD,), 0xA5, dtype=torch.uint8, device="cuda")
-    stream = torch.cuda.current_stream().cuda_stream
-    want, given, auto = dw0.clone(), dw0.clone(), dw0.clone()
-    # an explicit stream without a workspace: the unsplit call
-    hl.hilore_dequant_wgrad(codes, scales, code, block, dy, want, K, M, N, accumulate, stream=stream)
+    want, given, auto, side = dw0.clone(), dw0.clone(), dw0.clone(), dw0.clone()
+    torch.cuda.synchronize()
+    st = hl.load().hilore_dequant_wgrad(  # the unsplit call
+        codes.data_ptr(), scales.data_ptr() if block else None, code, block, dy.data_ptr(),
+        want.data_ptr(), K, M, N, int(accumulate), torch.cuda.current_stream().cuda_stream)
+    assert st == hl.HILORE_OK
     hl.hilore_dequant_wgrad(codes, scales, code, block, dy, given, K, M, N, accumulate,
                             workspace=buf[:need])
     hl.hilore_dequant_wgrad(codes, scales, code, block, dy, auto, K, M, N, accumulate)
+    stream = torch.cuda.Stream()
+    hl.hilore_dequant_wgrad(codes, scales, code, block, dy, side, K, M, N, accumulate,
+                            stream=stream.cuda_stream)
     torch.cuda.synchronize()
     ref = x[:, :8].double().t().contiguous() @ dy.double()
     if accumulate:
         ref += dw0[:8].double()
     assert np.array_equal(want[:8].double().cpu().numpy(), ref.cpu().numpy())
-    assert torch.equal(given, want) and torch.equal(auto, want)
+    assert torch.equal(given, want) and torch.equal(auto, want) and torch.equal(side, want)
     assert bool((buf[need:] == 0xA5).all())
+
+
+@pytest.mark.gpu
+def test_streams_and_capture(hl):
+    """General operands: default and explicit streams give the same bits, as does a
+    replayed graph; an explicit stream under capture takes the unsplit call."""
+    K, M, N = 2048, 896, 896
+    assert hl.hilore_wgrad_workspace_bytes(K, M, N) > 0
+    g = torch.Generator(device="cuda").manual_seed(5)
+    codes = torch.randn((K, M), generator=g, device="cuda").to(torch.float8_e4m3fn).view(torch.uint8)
+    scales = torch.rand((K, M // 128), generator=g, device="cuda") + 0.1
+    dy = torch.randn((K, N), generator=g, device="cuda").to(torch.bfloat16)
+    out = [torch.full((M, N), float("nan"), device="cuda") for _ in range(4)]
+    torch.cuda.synchronize()
+    call = lambda dw, **kw: hl.hilore_dequant_wgrad(codes, scales, 1, 128, dy, dw, K, M, N, **kw)  # noqa: E731
+    call(out[0])
+    side = torch.cuda.Stream()
+    call(out[1], stream=side.cuda_stream)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(out[2])
+        call(out[3], stream=torch.cuda.current_stream().cuda_stream)
+    for _ in range(3):
+        out[2].fill_(float("nan"))
+        out[3].fill_(float("nan"))
+        graph.replay()
+        call(out[1])
+        torch.cuda.synchronize()
+        assert torch.equal(out[0], out[1]) and torch.equal(out[0], out[2])
+        # the same products in one sum: fp32 rounding of 2048 terms
+        assert float((out[3] - out[0]).norm() / out[0].norm()) <= 4e-6
