@@ -178,7 +178,7 @@ hilore_status check_exposure_risk(const float *coeff, const uint8_t *mask, int64
 }
 
 // Partial sums of every (row chunk, unit) into part ([unit][chunk] layout),
-// then one fold launch over all units.
+// then one fold launch over all units (none for units of one chunk).
 hilore_status run_exposure_risk(const float *coeff, const uint8_t *mask, int64_t rows,
                                 const hilore_unit_desc *units, int n_units, float eps_alpha,
                                 float eps_rel, float *exposure, float *risk, float *rel_err,
@@ -191,6 +191,10 @@ hilore_status run_exposure_risk(const float *coeff, const uint8_t *mask, int64_t
     b.rows = rows;
     b.n_chunks = n_chunks;
     b.eps_alpha = eps_alpha;
+    b.eps_rel = eps_rel;
+    b.exposure = exposure + first;
+    b.risk = risk + first;
+    b.rel_err = rel_err + first;
     b.part = part + (int64_t)first * n_chunks * hilore::kRiskPartFloats;
     for (int i = first; i < n_units && b.n < hilore::kRiskUnitsPerLaunch; ++i) {
       b.ss_x[b.n] = units[i].row_ss_x;
@@ -201,6 +205,7 @@ hilore_status run_exposure_risk(const float *coeff, const uint8_t *mask, int64_t
     const hilore_status st = hip_status(hilore::launch_risk_partial(b, s));
     if (st != HILORE_OK) return st;
   }
+  if (n_chunks == 1) return HILORE_OK;  // the partial launches wrote the results
   return hip_status(hilore::launch_risk_fold(part, n_units, n_chunks, eps_alpha, eps_rel,
                                              exposure, risk, rel_err, s));
 }

@@ -90,14 +90,16 @@ struct RiskBatch {
   const float *ss_err[kRiskUnitsPerLaunch];
   float inv_cols[kRiskUnitsPerLaunch];  // 1 / d_u
   float *part;                          // partials of this launch's first unit
+  float *exposure, *risk, *rel_err;     // results of this launch's first unit (one chunk)
   const float *coeff;
   const uint8_t *mask;
   int64_t rows;
   int64_t n_chunks;
-  float eps_alpha;
+  float eps_alpha, eps_rel;
   int n;
 };
 int64_t risk_chunks(int64_t rows);
+// With one chunk per unit this writes the results and there is nothing to fold.
 hipError_t launch_risk_partial(const RiskBatch &b, hipStream_t s);
 hipError_t launch_risk_fold(const float *part, int n_units, int64_t n_chunks, float eps_alpha,
                             float eps_rel, float *exposure, float *risk, float *rel_err,
