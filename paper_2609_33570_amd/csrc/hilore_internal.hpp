@@ -215,6 +215,7 @@ struct LoraPlan {
   int64_t S, KS, U;  // strips of 256 columns, k-steps of 32 rows per strip, S * KS
   int64_t n_wg;      // workgroups of the main kernel
   int xcd_remap;     // give each XCD consecutive ranges
+  int slots;         // partials per workgroup: 2 where its range may meet two strips
   size_t workspace_bytes;
   int passes;        // 16 adapter rows per pass
 };
@@ -224,13 +225,13 @@ struct LoraArgs {
   const float *scales;
   const uint16_t *dh;  // bf16 [K, ldh]
   float *da;           // f32 [r, M]
-  float *part;         // workspace: 2 partial [16][256] slots per workgroup
+  float *part;         // workspace: `slots` partial [16 R][256] slots per workgroup
   int64_t K, M;
   int ldh, r0, r_pass;
   float scale;
   int accumulate;
   int64_t S, KS, U, n_wg;
-  int xcd_remap;
+  int xcd_remap, slots;
 };
 hipError_t launch_lora(const LoraArgs &a, int code, int block, int r, hipStream_t s);
 

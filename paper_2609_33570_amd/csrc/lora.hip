@@ -357,7 +357,7 @@ __global__ __launch_bounds__(kThreads, 1) void lora_wave_kernel(const LoraArgs a
         *reinterpret_cast<f32x4 *>(&mine[(4 * h + v) * kStrip + 16 * q + 4 * c4]) =
             f32x4{acc[4 * c4][v], acc[4 * c4 + 1][v], acc[4 * c4 + 2][v], acc[4 * c4 + 3][v]};
     __syncthreads();
-    float *out = a.part + (2 * wg + seg) * (int64_t)kPart;
+    float *out = a.part + (a.slots * wg + seg) * (int64_t)kPart;
 #pragma unroll
     for (int e4 = 0; e4 < kPart / 4 / kThreads; ++e4) {
       const int e = 4 * (tid + e4 * kThreads);
@@ -585,7 +585,7 @@ __global__ __launch_bounds__(kThreads, 1) void lora_slab_kernel(const LoraArgs a
 
     // acc[rb][c][v] = dA[16 rb + 4h + v][128 half + 8 q + c] of this wave's
     // k-steps; the four pairs are added in order, one row block at a time
-    float *out = a.part + (2 * wg + seg) * kSlot;
+    float *out = a.part + (a.slots * wg + seg) * kSlot;
 #pragma unroll
     for (int rb = 0; rb < R; ++rb) {
       float *mine = red[wave];
@@ -801,7 +801,7 @@ __global__ __launch_bounds__(kThreads, 1) void lora_coop_kernel(const LoraArgs a
     // segment writes them
     __syncthreads();
     // acc[rb][gi][v] = dA[16 rb + 4 h + v][16 (2 wave + gi) + q]
-    float *out = a.part + (2 * wg + seg) * kSlot;
+    float *out = a.part + (a.slots * wg + seg) * kSlot;
 #pragma unroll
     for (int rb = 0; rb < R; ++rb)
 #pragma unroll
@@ -823,6 +823,8 @@ __global__ __launch_bounds__(kThreads, 1) void lora_coop_kernel(const LoraArgs a
 // earlier strip, and then holds this strip's sums in its second slot.
 constexpr int kReduceBatch = 16;
 
+// SLOTS: partials per workgroup (a.slots; as a load it cost every call 0.2 us).
+template <int SLOTS>
 __global__ __launch_bounds__(256) void lora_reduce_kernel(const LoraArgs a) {
   const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
   constexpr int kQuads = kStrip / 4;
@@ -838,16 +840,17 @@ __global__ __launch_bounds__(256) void lora_reduce_kernel(const LoraArgs a) {
     const int64_t first = s * a.KS;
     const int64_t w0 = ((first + 1) * a.n_wg - 1) / a.U;
     const int64_t w1 = ((first + a.KS) * a.n_wg - 1) / a.U;  // inclusive
-    const float *base = a.part + rr * kStrip + c4;
-    sum = *reinterpret_cast<const f32x4 *>(
-        base + (2 * w0 + (range_begin(a, w0) < first ? 1 : 0)) * slot);
+    const int64_t step = SLOTS * slot;  // from one workgroup's first partial to the next's
+    const float *at = a.part + rr * kStrip + c4 + w0 * step;
+    sum = *reinterpret_cast<const f32x4 *>(range_begin(a, w0) < first ? at + slot : at);
+    at += step;
     // up to 16 partials per round trip (a narrow unit's strip has up to 18
     // parts); the additions stay in ascending workgroup order
-    for (int64_t w = w0 + 1; w <= w1; w += kReduceBatch) {
+    for (int64_t w = w0 + 1; w <= w1; w += kReduceBatch, at += kReduceBatch * step) {
       f32x4 x[kReduceBatch];
 #pragma unroll
       for (int k = 0; k < kReduceBatch; ++k)
-        x[k] = w + k <= w1 ? *reinterpret_cast<const f32x4 *>(base + 2 * (w + k) * slot)
+        x[k] = w + k <= w1 ? *reinterpret_cast<const f32x4 *>(at + k * step)
                            : f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int k = 0; k < kReduceBatch; ++k) sum += x[k];
@@ -913,23 +916,30 @@ LoraPlan lora_plan(int64_t K, int64_t M, int r) {
   p.n_wg = p.U < want ? p.U : want;
   // an XCD's share of the strips is at least 1 KB of every row from 32 strips on
   p.xcd_remap = p.n_wg % 8 == 0 && p.S >= 32 ? 1 : 0;
-  // Narrow units (fewer than 32 strips, e.g. a hidden-width input): every strip
-  // is split into `parts` equal ranges, one per workgroup, so no range crosses a
-  // strip (one partial each) and the waves' k-steps come in whole ring pairs.
-  // The pairs per wave are the fewest that S * parts <= 256 workgroups allow,
-  // and `parts` the smallest count that reaches them.  On 16384 x 3584 (14
-  // strips) this gives 224 workgroups of 32 k-steps.
-  if (p.S < 32 && p.KS >= 2 * kWaves) {
-    const int64_t per = 2 * kWaves;  // k-steps of one ring pair of every wave
-    const int64_t pmax = kLoraWorkgroups / p.S;
-    const int64_t pairs = (p.KS + per * pmax - 1) / (per * pmax);
-    const int64_t parts = (p.KS + per * pairs - 1) / (per * pairs);
-    p.n_wg = p.S * parts;
-  }
   // passes of up to 80 adapter rows; the widest sets the partial slot size
   const int widest = pass_blocks(r < kRows * kMaxR ? r : kRows * kMaxR);
-  p.workspace_bytes =
-      (size_t)(p.n_wg > 0 ? p.n_wg : 1) * 2 * (size_t)(kRows * widest * kStrip) * sizeof(float);
+  p.slots = 2;
+  // Narrow units (fewer than 32 strips, e.g. a hidden-width input): every strip
+  // is split into `parts` equal ranges, one per workgroup, so no range crosses a
+  // strip (one partial each).  A range is whole rounds of the kernel's k-steps,
+  // the fewest that S * parts <= 256 workgroups allow, and `parts` the smallest
+  // count that reaches them.  A round is two k-steps of every wave of the per-wave
+  // kernel (16) or pair of the slab kernel (8), and 4 k-steps for the cooperative
+  // one: on 13001 x 3584 rounds of 16 leave 74 of 256 CUs without a workgroup,
+  // finer ones 18 (fp8 1x128, r = 32 / 48 / 64 / 80: 23.0 / 25.0 / 26.7 / 32.3 ->
+  // 21.1 / 23.5 / 25.6 / 29.6 us; with one adapter block finer rounds gain on some
+  // sizes and lose on others, 19.5 -> 18.6 us on 10007 x 3584, 14.3 -> 17.2 on
+  // 16384 x 896).
+  const int64_t per = widest == 1 ? 2 * kWaves : widest < kMaxR ? 2 * kPairs : kPairs;
+  if (p.S < 32 && p.KS >= 2 * kWaves) {
+    const int64_t pmax = kLoraWorkgroups / p.S;
+    const int64_t rounds = (p.KS + per * pmax - 1) / (per * pmax);
+    const int64_t parts = (p.KS + per * rounds - 1) / (per * rounds);
+    p.n_wg = p.S * parts;
+    p.slots = 1;
+  }
+  p.workspace_bytes = (size_t)(p.n_wg > 0 ? p.n_wg : 1) * (size_t)p.slots *
+                      (size_t)(kRows * widest * kStrip) * sizeof(float);
   p.passes = (r + kRows * kMaxR - 1) / (kRows * kMaxR);
   return p;
 }
@@ -945,8 +955,9 @@ hipError_t launch_lora(const LoraArgs &base, int code, int block, int r, hipStre
       else dispatch<kCodeE4M3>(a, block, s);
     }
     const int64_t threads = a.S * a.r_pass * (kStrip / 4);
-    hipLaunchKernelGGL(lora_reduce_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0,
-                       s, a);
+    const dim3 grid((unsigned)((threads + 255) / 256));
+    if (a.slots == 1) hipLaunchKernelGGL(lora_reduce_kernel<1>, grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL(lora_reduce_kernel<2>, grid, dim3(256), 0, s, a);
   }
   return hipGetLastError();
 }
