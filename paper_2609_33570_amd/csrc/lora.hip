@@ -932,9 +932,16 @@ LoraPlan lora_plan(int64_t K, int64_t M, int r) {
   // 16384 x 896).
   const int64_t per = widest == 1 ? 2 * kWaves : widest < kMaxR ? 2 * kPairs : kPairs;
   if (p.S < 32 && p.KS >= 2 * kWaves) {
+    // count in whole rounds of `step` k-steps, at most `most` of them
+    auto split = [&](int64_t step, int64_t most) {
+      const int64_t rounds = (p.KS + step * most - 1) / (step * most);
+      return (p.KS + step * rounds - 1) / (step * rounds);
+    };
     const int64_t pmax = kLoraWorkgroups / p.S;
-    const int64_t rounds = (p.KS + per * pmax - 1) / (per * pmax);
-    const int64_t parts = (p.KS + per * rounds - 1) / (per * rounds);
+    // at most twice the parts of 16 k-steps: short units gain nothing from more
+    // partial sums, and one partial each then never needs more workspace than two
+    const int64_t cap = 2 * split(2 * kWaves, pmax);
+    const int64_t parts = split(per, cap < pmax ? cap : pmax);
     p.n_wg = p.S * parts;
     p.slots = 1;
   }
