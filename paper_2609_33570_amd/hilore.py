@@ -181,14 +181,13 @@ def unit_desc(x=None, codes=None, scales=None, xhat=None, row_ss_x=None, row_ss_
 
 def _desc_array(units: Sequence[hilore_unit_desc]):
     n = len(units)
-    if n < 4:
-        return (hilore_unit_desc * max(1, n))(*units), n
-    # from about 4 units on one copy of the joined structs beats filling the
-    # array element by element (78 units: about 10 us less)
-    for t in set(map(type, units)):
-        if not issubclass(t, hilore_unit_desc):
-            raise TypeError(f"expected hilore_unit_desc instances, got {t.__name__}")
-    return (hilore_unit_desc * n).from_buffer_copy(b"".join(units)), n
+    # from about 4 units on one copy of the joined structs beats filling the array
+    # element by element (78 units: about 10 us less).  Their bytes are the array's
+    # only where every unit is of this very type: a subclass may be longer, and a
+    # ctypes array also takes tuples.
+    if n >= 4 and set(map(type, units)) == {hilore_unit_desc}:
+        return (hilore_unit_desc * n).from_buffer_copy(b"".join(units)), n
+    return (hilore_unit_desc * max(1, n))(*units), n
 
 
 # ---------------------------------------------------------------- entry points --
