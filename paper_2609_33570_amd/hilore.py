@@ -100,6 +100,9 @@ def load() -> ctypes.CDLL:
         fn = getattr(L, name)
         fn.restype = res
         fn.argtypes = args
+    # of the HIP runtime that the library is linked with
+    L.hipStreamIsCapturing.restype = i32
+    L.hipStreamIsCapturing.argtypes = [P, P]
     _lib = L
     return L
 
@@ -275,20 +278,26 @@ def hilore_wgrad_workspace_bytes(K: int, M: int, N: int) -> int:
     return int(load().hilore_wgrad_workspace_bytes(int(K), int(M), int(N)))
 
 
-def _wgrad_workspace(nbytes: int, device, stream):
-    """A buffer from torch's allocator in the order of the call's stream (an explicit
-    one has a pool of its own there, so the buffer's reuse follows that stream's work),
-    or None: no memory left, or an explicit stream under capture, whose graph would
-    keep using a buffer that the allocator gives to others."""
+def _wgrad_scratch(nbytes: int, dw, stream, handle: int):
+    """Device memory for one call, from torch's pool of the call's stream: (pointer,
+    tensor that holds it, or None where the caller gives it back), or None where there
+    is none.  It goes back as soon as the call is enqueued: torch gives a block again
+    only in the order of the stream that it was taken for.  (An explicit stream's
+    blocks, at most 128 MB a call, stay cached for that stream until
+    torch.cuda.empty_cache().  Taking them so costs the host 2 us a call, a stream
+    context around torch.empty 10.)"""
     import torch
 
+    device = dw.device
     try:
-        if stream is None:
-            return torch.empty(nbytes, dtype=torch.uint8, device=device)
-        with torch.cuda.stream(torch.cuda.ExternalStream(int(stream), device=device)):
-            if torch.cuda.is_current_stream_capturing():
+        if stream is not None:  # a graph would keep using what goes back here
+            status = ctypes.c_int(0)
+            if load().hipStreamIsCapturing(handle, ctypes.byref(status)) != 0 or status.value != 0:
                 return None
-            return torch.empty(nbytes, dtype=torch.uint8, device=device)
+        if stream is None:
+            buf = torch.empty(nbytes, dtype=torch.uint8, device=device)
+            return buf.data_ptr(), buf
+        return torch.cuda.caching_allocator_alloc(nbytes, device, handle), None
     except torch.cuda.OutOfMemoryError:
         return None
 
@@ -296,22 +305,33 @@ def _wgrad_workspace(nbytes: int, device, stream):
 def hilore_dequant_wgrad(x_codes, x_scales, code, block: int, dy, dw, K: int, M: int, N: int,
                          accumulate: bool = False, stream=None, workspace=None):
     """workspace: a device tensor of at least hilore_wgrad_workspace_bytes(K, M, N) bytes
-    for the partial sums of split tiles.  None: a buffer of that size from torch's
-    allocator, or the unsplit call where that cannot be had (no memory left, an explicit
-    stream under capture)."""
+    for the partial sums of split tiles.
+
+    None: memory of that size from torch's allocator for the duration of the call.  Where
+    that cannot be had the call runs unsplit, as it does in C without a workspace, and
+    the split tiles' sums are rounded otherwise: on an explicit stream under capture and
+    where memory runs out."""
     L = load()
     args = (_p(x_codes), _p(x_scales), _code(code), int(block), _p(dy), _p(dw), int(K), int(M),
             int(N), 1 if accumulate else 0)
-    if workspace is None:
-        need = L.hilore_wgrad_workspace_bytes(args[6], args[7], args[8])
-        if need:
-            workspace = _wgrad_workspace(need, dw.device, stream)
-    if workspace is None:
-        st = L.hilore_dequant_wgrad(*args, _stream(stream))
-    else:
+    handle = _stream(stream)
+    if workspace is not None:
         st = L.hilore_dequant_wgrad_ws(*args, _p(workspace),
-                                       workspace.numel() * workspace.element_size(),
-                                       _stream(stream))
+                                       workspace.numel() * workspace.element_size(), handle)
+    else:
+        need = L.hilore_wgrad_workspace_bytes(args[6], args[7], args[8])
+        scratch = _wgrad_scratch(need, dw, stream, handle) if need else None
+        if scratch is None:
+            st = L.hilore_dequant_wgrad(*args, handle)
+        else:
+            ptr, buf = scratch
+            try:
+                st = L.hilore_dequant_wgrad_ws(*args, ptr, need, handle)
+            finally:
+                if buf is None:
+                    import torch
+
+                    torch.cuda.caching_allocator_delete(ptr)
     _check("hilore_dequant_wgrad", st)
 
 

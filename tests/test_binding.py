@@ -2,6 +2,7 @@
 import ctypes
 
 import pytest
+import torch
 
 from paper_2609_33570_amd import hilore
 
@@ -40,3 +41,105 @@ def test_descriptor_array(make, n):
 def test_descriptor_array_refuses_other_types(n):
     with pytest.raises(TypeError):
         hilore._desc_array([ctypes.c_int64(3)] * n)
+
+
+# --------------------------------------------- memory of the split weight gradient --
+NEED, OWN_STREAM, SCRATCH = 1 << 21, 0x5150, 1 << 30
+
+
+class FakeTensor:
+    """What the binding asks of a device tensor."""
+
+    is_cuda = True
+
+    def __init__(self, device=0):
+        self.device = torch.device("cuda", device)
+
+    def is_contiguous(self):
+        return True
+
+    def data_ptr(self):
+        return 1 << 20
+
+
+class FakeLibrary:
+    """Records which entry point the binding calls and with what memory."""
+
+    def __init__(self, capturing, need):
+        self.capturing, self.need, self.calls = capturing, need, []
+
+    def hilore_wgrad_workspace_bytes(self, K, M, N):
+        return self.need
+
+    def hipStreamIsCapturing(self, stream, status):
+        status._obj.value = 1 if self.capturing else 0
+        return 0
+
+    def hilore_dequant_wgrad(self, *args):
+        self.calls.append(("unsplit", None, args[10]))
+        return hilore.HILORE_OK if args[5] else hilore.HILORE_ERR_INVALID_ARG
+
+    def hilore_dequant_wgrad_ws(self, *args):
+        self.calls.append(("split", args[10:12], args[12]))
+        return hilore.HILORE_OK
+
+    def hilore_status_string(self, status):
+        return b"status"
+
+
+@pytest.fixture
+def fake(monkeypatch):
+    """hilore_dequant_wgrad on a host without a GPU: the library and torch's allocator faked."""
+    state = {"live": {}, "taken": []}
+
+    def alloc(size, device=None, stream=None):
+        if size >= state.get("limit", 1 << 40):
+            raise torch.cuda.OutOfMemoryError("no memory left")
+        device = torch.device(device).index if not isinstance(device, int) else device
+        state["taken"].append((size, device, stream))
+        p = SCRATCH + len(state["taken"]) * 4096
+        state["live"][p] = size
+        return p
+
+    monkeypatch.setattr(torch.cuda, "caching_allocator_alloc", alloc)
+    monkeypatch.setattr(torch.cuda, "caching_allocator_delete", lambda p: state["live"].pop(p))
+
+    class Tensor:
+        def __init__(self, n, dtype, device):
+            self.p = alloc(n, device, OWN_STREAM)
+
+        def data_ptr(self):
+            return self.p
+
+        def __del__(self):
+            if hasattr(self, "p"):
+                state["live"].pop(self.p)
+
+    monkeypatch.setattr(torch, "empty", Tensor)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda d: OWN_STREAM, raising=False)
+    monkeypatch.setattr(torch.cuda, "memory_snapshot", lambda: [
+        {"address": SCRATCH, "total_size": 1 << 21, "segment_pool_id": state.get("pool", (0, 0))}])
+
+    def call(capturing=False, need=NEED, dw=FakeTensor(), **kw):
+        lib = FakeLibrary(capturing, need)
+        monkeypatch.setattr(hilore, "load", lambda: lib)
+        x = FakeTensor()
+        try:
+            hilore.hilore_dequant_wgrad(x, x, 1, 128, x, dw, 16384, 3584, 512, **kw)
+        finally:
+            assert not state["live"], "memory kept after the call"
+        (entry,) = lib.calls
+        return entry
+
+    call.state = state
+    return call
+
+
+@pytest.mark.parametrize("kw,stream", [({}, OWN_STREAM), ({"stream": 77}, 77)], ids=["current", "explicit"])
+def test_wgrad_scratch_in_stream_order(fake, kw, stream):
+    """Taken for the call's stream, handed over whole, given back when the call is enqueued."""
+    name, (ptr, nbytes), handle = fake(**kw)
+    assert name == "split" and nbytes == NEED and ptr > SCRATCH and handle == stream
+    assert fake.state["taken"] == [(NEED, 0, stream)]
+    assert fake(need=0, **kw) == ("unsplit", None, stream) and len(fake.state["taken"]) == 1
