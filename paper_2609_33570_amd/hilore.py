@@ -278,6 +278,24 @@ def hilore_wgrad_workspace_bytes(K: int, M: int, N: int) -> int:
     return int(load().hilore_wgrad_workspace_bytes(int(K), int(M), int(N)))
 
 
+def _graph_owns(device, handle: int) -> bool:
+    """Whether what torch's allocator gives to a captured stream stays with the graph.
+    Under torch.cuda.graph it comes from the graph's own pool.  Under a capture that
+    torch has not begun (hipStreamBeginCapture) it comes from the ordinary pool, which
+    gives it to other tensors while the graph's replays still write it.  One byte is
+    taken to see from which (about 0.1 ms, captured calls only).  (A pool that the
+    program itself has put into use counts as the graph's: it is the program's to keep.)"""
+    import torch
+
+    p = torch.cuda.caching_allocator_alloc(1, device, handle)
+    try:
+        return any(s["address"] <= p < s["address"] + s["total_size"]
+                   and tuple(s.get("segment_pool_id", (0, 0))) != (0, 0)
+                   for s in torch.cuda.memory_snapshot())
+    finally:
+        torch.cuda.caching_allocator_delete(p)
+
+
 def _wgrad_scratch(nbytes: int, dw, stream, handle: int):
     """Device memory for one call, from torch's pool of the call's stream: (pointer,
     tensor that holds it, or None where the caller gives it back), or None where there
@@ -290,9 +308,11 @@ def _wgrad_scratch(nbytes: int, dw, stream, handle: int):
 
     device = dw.device
     try:
-        if stream is not None:  # a graph would keep using what goes back here
+        if handle:  # the null stream cannot be captured
             status = ctypes.c_int(0)
-            if load().hipStreamIsCapturing(handle, ctypes.byref(status)) != 0 or status.value != 0:
+            if load().hipStreamIsCapturing(handle, ctypes.byref(status)) != 0:
+                return None
+            if status.value != 0 and not _graph_owns(device, handle):
                 return None
         if stream is None:
             buf = torch.empty(nbytes, dtype=torch.uint8, device=device)
@@ -309,8 +329,9 @@ def hilore_dequant_wgrad(x_codes, x_scales, code, block: int, dy, dw, K: int, M:
 
     None: memory of that size from torch's allocator for the duration of the call.  Where
     that cannot be had the call runs unsplit, as it does in C without a workspace, and
-    the split tiles' sums are rounded otherwise: on an explicit stream under capture and
-    where memory runs out."""
+    the split tiles' sums are rounded otherwise: under a capture of the stream that torch
+    has not begun and where memory runs out.  A program that needs
+    the same bits there too gives a workspace in every call."""
     L = load()
     args = (_p(x_codes), _p(x_scales), _code(code), int(block), _p(dy), _p(dw), int(K), int(M),
             int(N), 1 if accumulate else 0)

@@ -143,3 +143,13 @@ def test_wgrad_scratch_in_stream_order(fake, kw, stream):
     assert name == "split" and nbytes == NEED and ptr > SCRATCH and handle == stream
     assert fake.state["taken"] == [(NEED, 0, stream)]
     assert fake(need=0, **kw) == ("unsplit", None, stream) and len(fake.state["taken"]) == 1
+
+
+@pytest.mark.parametrize("kw", [{}, {"stream": 77}], ids=["current", "explicit"])
+def test_wgrad_under_capture(fake, kw):
+    """A graph keeps writing a captured call's memory: it may come from a graph's own pool
+    only, and without one (a capture that torch has not begun) the call takes none."""
+    fake.state["pool"] = (0, 0)
+    assert fake(capturing=True, **kw)[0] == "unsplit"
+    fake.state["pool"] = (3, 0)
+    assert fake(capturing=True, **kw)[0] == "split"

@@ -88,16 +88,29 @@ def test_split_matches_unsplit(hl, code, block, K, M, N, accumulate):
     assert bool((buf[need:] == 0xA5).all())
 
 
-@pytest.mark.gpu
-def test_streams_and_capture(hl):
-    """General operands: default and explicit streams give the same bits, as does a
-    replayed graph; an explicit stream under capture takes the unsplit call."""
-    K, M, N = 2048, 896, 896
+def general(hl, K, M, N):
     assert hl.hilore_wgrad_workspace_bytes(K, M, N) > 0
     g = torch.Generator(device="cuda").manual_seed(5)
     codes = torch.randn((K, M), generator=g, device="cuda").to(torch.float8_e4m3fn).view(torch.uint8)
     scales = torch.rand((K, M // 128), generator=g, device="cuda") + 0.1
-    dy = torch.randn((K, N), generator=g, device="cuda").to(torch.bfloat16)
+    return codes, scales, torch.randn((K, N), generator=g, device="cuda").to(torch.bfloat16)
+
+
+def unsplit(hl, codes, scales, dy, K, M, N):
+    dw = torch.full((M, N), float("nan"), device="cuda")
+    st = hl.load().hilore_dequant_wgrad(codes.data_ptr(), scales.data_ptr(), 1, 128, dy.data_ptr(),
+                                        dw.data_ptr(), K, M, N, 0,
+                                        torch.cuda.current_stream().cuda_stream)
+    assert st == hl.HILORE_OK
+    return dw
+
+
+@pytest.mark.gpu
+def test_streams_and_capture(hl):
+    """General operands: default and explicit streams give the same bits, as does a
+    graph replayed from either."""
+    K, M, N = 2048, 896, 896
+    codes, scales, dy = general(hl, K, M, N)
     out = [torch.full((M, N), float("nan"), device="cuda") for _ in range(4)]
     torch.cuda.synchronize()
     call = lambda dw, **kw: hl.hilore_dequant_wgrad(codes, scales, 1, 128, dy, dw, K, M, N, **kw)  # noqa: E731
@@ -115,6 +128,41 @@ def test_streams_and_capture(hl):
         graph.replay()
         call(out[1])
         torch.cuda.synchronize()
-        assert torch.equal(out[0], out[1]) and torch.equal(out[0], out[2])
-        # the same products in one sum: fp32 rounding of 2048 terms
-        assert float((out[3] - out[0]).norm() / out[0].norm()) <= 4e-6
+        for o in out[1:]:
+            assert torch.equal(out[0], o)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("explicit", [False, True], ids=["current", "explicit"])
+def test_capture_not_begun_by_torch(hl, explicit):
+    """hipStreamBeginCapture: torch gives the graph no pool of its own, so the call takes no
+    memory and runs unsplit; a tensor in the memory it would have been given stays whole."""
+    K, M, N = 2048, 896, 896
+    codes, scales, dy = general(hl, K, M, N)
+    want = unsplit(hl, codes, scales, dy, K, M, N)
+    need = hl.hilore_wgrad_workspace_bytes(K, M, N)
+    dw = torch.full((M, N), float("nan"), device="cuda")
+    L, P = hl.load(), ctypes.c_void_p
+    side, graph, run = torch.cuda.Stream(), P(), P()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        torch.empty(need, dtype=torch.uint8, device="cuda")  # a free block of this size
+        torch.cuda.synchronize()
+        assert L.hipStreamBeginCapture(P(side.cuda_stream), 0) == 0
+        try:
+            hl.hilore_dequant_wgrad(codes, scales, 1, 128, dy, dw, K, M, N,
+                                    **({"stream": side.cuda_stream} if explicit else {}))
+        finally:
+            assert L.hipStreamEndCapture(P(side.cuda_stream), ctypes.byref(graph)) == 0
+        nodes = ctypes.c_size_t(0)
+        assert L.hipGraphGetNodes(graph, None, ctypes.byref(nodes)) == 0 and nodes.value == 1
+        other = torch.full((need,), 0xA5, dtype=torch.uint8, device="cuda")
+        assert L.hipGraphInstantiate(ctypes.byref(run), graph, None, None, ctypes.c_size_t(0)) == 0
+        try:
+            for _ in range(3):
+                dw.fill_(float("nan"))
+                assert L.hipGraphLaunch(run, P(side.cuda_stream)) == 0
+                torch.cuda.synchronize()
+                assert torch.equal(dw, want) and bool((other == 0xA5).all())
+        finally:
+            assert L.hipGraphExecDestroy(run) == 0 and L.hipGraphDestroy(graph) == 0
