@@ -306,7 +306,8 @@ def _wgrad_scratch(nbytes: int, dw, stream, handle: int):
     context around torch.empty 10.)"""
     import torch
 
-    device = dw.device
+    # the current stream belongs to the current device, wherever dw lives
+    device = torch.cuda.current_device() if stream is None else dw.device
     try:
         if handle:  # the null stream cannot be captured
             status = ctypes.c_int(0)

@@ -153,3 +153,11 @@ def test_wgrad_under_capture(fake, kw):
     assert fake(capturing=True, **kw)[0] == "unsplit"
     fake.state["pool"] = (3, 0)
     assert fake(capturing=True, **kw)[0] == "split"
+
+
+def test_wgrad_scratch_of_another_device(fake):
+    """The current stream orders the reuse of memory of its own device."""
+    assert fake(dw=FakeTensor(1))[0] == "split"
+    assert fake.state["taken"] == [(NEED, 0, OWN_STREAM)]
+    assert fake(dw=FakeTensor(1), stream=77)[0] == "split"
+    assert fake.state["taken"][1:] == [(NEED, 1, 77)]
