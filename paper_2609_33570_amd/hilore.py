@@ -342,7 +342,8 @@ def hilore_dequant_wgrad(x_codes, x_scales, code, block: int, dy, dw, K: int, M:
                                        workspace.numel() * workspace.element_size(), handle)
     else:
         need = L.hilore_wgrad_workspace_bytes(args[6], args[7], args[8])
-        scratch = _wgrad_scratch(need, dw, stream, handle) if need else None
+        # without dw the library refuses the call, or there is nothing to do
+        scratch = _wgrad_scratch(need, dw, stream, handle) if need and dw is not None else None
         if scratch is None:
             st = L.hilore_dequant_wgrad(*args, handle)
         else:

@@ -161,3 +161,10 @@ def test_wgrad_scratch_of_another_device(fake):
     assert fake.state["taken"] == [(NEED, 0, OWN_STREAM)]
     assert fake(dw=FakeTensor(1), stream=77)[0] == "split"
     assert fake.state["taken"][1:] == [(NEED, 1, 77)]
+
+
+def test_wgrad_without_output(fake):
+    """A call without dw is the library's to refuse."""
+    with pytest.raises(hilore.HiloreError) as e:
+        fake(dw=None, stream=0)
+    assert e.value.status == hilore.HILORE_ERR_INVALID_ARG and not fake.state["taken"]
