@@ -10,6 +10,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 from typing import Optional, Sequence
 
 from . import defaults as _d
@@ -320,6 +321,9 @@ def _wgrad_scratch(nbytes: int, dw, stream, handle: int):
             return buf.data_ptr(), buf
         return torch.cuda.caching_allocator_alloc(nbytes, device, handle), None
     except torch.cuda.OutOfMemoryError:
+        warnings.warn(f"hilore_dequant_wgrad: no {nbytes} bytes left for the partial sums; the "
+                      "unsplit call takes their place and rounds differently", RuntimeWarning,
+                      stacklevel=3)
         return None
 
 
@@ -331,7 +335,7 @@ def hilore_dequant_wgrad(x_codes, x_scales, code, block: int, dy, dw, K: int, M:
     None: memory of that size from torch's allocator for the duration of the call.  Where
     that cannot be had the call runs unsplit, as it does in C without a workspace, and
     the split tiles' sums are rounded otherwise: under a capture of the stream that torch
-    has not begun and where memory runs out.  A program that needs
+    has not begun and, with a RuntimeWarning, where memory runs out.  A program that needs
     the same bits there too gives a workspace in every call."""
     L = load()
     args = (_p(x_codes), _p(x_scales), _code(code), int(block), _p(dy), _p(dw), int(K), int(M),

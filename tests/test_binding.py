@@ -168,3 +168,11 @@ def test_wgrad_without_output(fake):
     with pytest.raises(hilore.HiloreError) as e:
         fake(dw=None, stream=0)
     assert e.value.status == hilore.HILORE_ERR_INVALID_ARG and not fake.state["taken"]
+
+
+@pytest.mark.parametrize("kw", [{}, {"stream": 77}], ids=["current", "explicit"])
+def test_wgrad_out_of_memory(fake, kw):
+    """Runs unsplit, whose rounding differs, and says so."""
+    fake.state["limit"] = NEED
+    with pytest.warns(RuntimeWarning, match="unsplit"):
+        assert fake(**kw)[0] == "unsplit"

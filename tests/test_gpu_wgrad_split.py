@@ -166,3 +166,23 @@ def test_capture_not_begun_by_torch(hl, explicit):
                 assert torch.equal(dw, want) and bool((other == 0xA5).all())
         finally:
             assert L.hipGraphExecDestroy(run) == 0 and L.hipGraphDestroy(graph) == 0
+
+
+@pytest.mark.gpu
+def test_out_of_memory(hl):
+    """No memory left for the partial sums: the unsplit call, with a warning."""
+    K, M, N = 2048, 896, 896
+    codes, scales, dy = general(hl, K, M, N)
+    want = unsplit(hl, codes, scales, dy, K, M, N)
+    dw = torch.full((M, N), float("nan"), device="cuda")
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    try:
+        torch.cuda.set_per_process_memory_fraction(
+            (torch.cuda.memory_reserved() + 1) / torch.cuda.mem_get_info()[1])
+        with pytest.warns(RuntimeWarning, match="unsplit"):
+            hl.hilore_dequant_wgrad(codes, scales, 1, 128, dy, dw, K, M, N)
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    torch.cuda.synchronize()
+    assert torch.equal(dw, want)
