@@ -31,6 +31,8 @@ HILORE_CODE_FP8_E4M3FN_CAST = 2  # the paper's literal codec: plain cast, no sca
 CODES = {"int8": HILORE_CODE_INT8, "e4m3fn": HILORE_CODE_FP8_E4M3FN,
          "e4m3fn_cast": HILORE_CODE_FP8_E4M3FN_CAST}
 
+_STREAM_PER_THREAD = 2  # hipStreamPerThread
+
 
 class HiloreError(RuntimeError):
     def __init__(self, fn: str, status: int):
@@ -307,6 +309,8 @@ def _wgrad_scratch(nbytes: int, dw, stream, handle: int):
     context around torch.empty 10.)"""
     import torch
 
+    if handle == _STREAM_PER_THREAD:  # one handle, another stream in every thread
+        return None
     # the current stream belongs to the current device, wherever dw lives
     device = torch.cuda.current_device() if stream is None else dw.device
     try:
@@ -335,8 +339,8 @@ def hilore_dequant_wgrad(x_codes, x_scales, code, block: int, dy, dw, K: int, M:
     None: memory of that size from torch's allocator for the duration of the call.  Where
     that cannot be had the call runs unsplit, as it does in C without a workspace, and
     the split tiles' sums are rounded otherwise: under a capture of the stream that torch
-    has not begun and, with a RuntimeWarning, where memory runs out.  A program that needs
-    the same bits there too gives a workspace in every call."""
+    has not begun, on hipStreamPerThread, and, with a RuntimeWarning, where memory runs
+    out.  A program that needs the same bits there too gives a workspace in every call."""
     L = load()
     args = (_p(x_codes), _p(x_scales), _code(code), int(block), _p(dy), _p(dw), int(K), int(M),
             int(N), 1 if accumulate else 0)

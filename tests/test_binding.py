@@ -176,3 +176,8 @@ def test_wgrad_out_of_memory(fake, kw):
     fake.state["limit"] = NEED
     with pytest.warns(RuntimeWarning, match="unsplit"):
         assert fake(**kw)[0] == "unsplit"
+
+
+def test_wgrad_on_the_per_thread_stream(fake):
+    """One handle stands for a stream of every thread: no order among its calls."""
+    assert fake(stream=2) == ("unsplit", None, 2) and not fake.state["taken"]
