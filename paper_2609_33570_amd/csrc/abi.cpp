@@ -87,21 +87,17 @@ hilore_status run_codec(const hilore_unit_desc *units, int n_units, int code, in
   // consecutive units that share a row mapping go to one launch (at most
   // kUnitsPerLaunch units, kRowsPerLaunch rows and, unless one unit alone is
   // larger, kElemsPerLaunch elements per launch)
-  int64_t call_rows = 0;
-  for (int i = 0; i < n_units; ++i)
-    if (units[i].cols > 0) call_rows += units[i].rows;
   CodecBatch b{};
-  int64_t rows = 0, elems = 0;  // rows: groups of rows where a wave takes several
+  int64_t rows = 0, elems = 0;
   bool any_stats = false;
   auto flush = [&]() -> hilore_status {
     if (b.n == 0) return HILORE_OK;
-    b.row_begin[b.n] = rows;
+    hilore::codec_number_rows(b, (use & kUseX) != 0);
     b.stats = any_stats ? 1 : 0;
     const hilore_status st = hip_status(launch(b));
-    const int wl = b.wpr_log2, rl = b.rpw_log2;
+    const int wl = b.wpr_log2;
     b = CodecBatch{};
     b.wpr_log2 = wl;
-    b.rpw_log2 = rl;
     rows = 0;
     elems = 0;
     any_stats = false;
@@ -111,17 +107,13 @@ hilore_status run_codec(const hilore_unit_desc *units, int n_units, int code, in
     const hilore_unit_desc &u = units[i];
     if (u.rows == 0 || u.cols == 0) continue;
     const int wl = hilore::codec_wpr_log2(u.cols, lane_steps);
-    const int rl = hilore::codec_rpw_log2(u.cols, (use & kUseX) != 0 ? u.ld : u.cols, call_rows);
-    const int64_t groups = (u.rows + (int64_t(1) << rl) - 1) >> rl;
-    if (b.n == hilore::kUnitsPerLaunch ||
-        (b.n > 0 && (wl != b.wpr_log2 || rl != b.rpw_log2)) ||
-        rows + groups > hilore::kRowsPerLaunch ||
+    if (b.n == hilore::kUnitsPerLaunch || (b.n > 0 && wl != b.wpr_log2) ||
+        rows + u.rows > hilore::kRowsPerLaunch ||
         (b.n > 0 && elems + u.rows * u.cols > hilore::kElemsPerLaunch)) {
       const hilore_status st = flush();
       if (st != HILORE_OK) return st;
     }
     b.wpr_log2 = wl;
-    b.rpw_log2 = rl;
     CodecUnit &c = b.u[b.n];
     c.x = u.x;
     c.codes = static_cast<uint8_t *>(u.codes);
@@ -133,8 +125,7 @@ hilore_status run_codec(const hilore_unit_desc *units, int n_units, int code, in
     c.cols = u.cols;
     c.ld = u.ld;
     any_stats = any_stats || c.ss_x || c.ss_err;
-    b.row_begin[b.n] = rows;
-    rows += groups;
+    rows += u.rows;
     elems += u.rows * u.cols;
     ++b.n;
   }

@@ -21,7 +21,7 @@
 // workgroups that each cover a few KiB to a few tens of KiB of one row keep
 // the addresses in flight across the chip inside a narrow moving window,
 // which the HBM serves far better than thousands of waves each walking its
-// own row.  Narrow rows (up to 1024 columns) of large calls are taken several to
+// own row.  Narrow rows (up to 1024 columns) of large launches are taken several to
 // a wave, see RowGroup.  The optional per-row sums are kept per lane in a fixed order,
 // reduced per wave with a butterfly and across the row's waves in wave
 // order, so they depend only on the row length.
@@ -468,35 +468,47 @@ __global__ __launch_bounds__(kMaxThreads) void decompress_kernel(const CodecBatc
 
 // Narrow rows: a wave takes a group of (4 / S) H consecutive rows of one unit in
 // its four loads, S loads per row (S = 1, 2) or H rows per load (H = 1, 2; then
-// S = 1 and a row has 32 lanes).  row_begin counts groups.  One buffer range
-// covers the group; lanes past a row's end or past the unit's last row take an
-// offset outside it.  Every value and every row's sums are formed by the same
-// operations in the same order as with one row per wave.
-// Against that, fp8 1x128, encode with sums / decode: 16384 x 256 x 8 units 59 -> 22
-// / 39 -> 19 us, 16384 x 512 x 8 62 -> 42 / 45 -> 34, 16384 x 896 x 6 64 -> 51 / 46
-// -> 45 (16, 33 and 43 us at the copy rate).
+// S = 1 and a row has 32 lanes).  S = 4 is one row per wave, in as many rounds of
+// four loads as it needs.  The group size belongs to the unit (rpw_log2), so units
+// of all narrow widths share a launch: RPW is the size that they agree on, or -1
+// and the wave branches once, on a scalar (24 x 1024 x (896, 128, 128, 896), fp8
+// 1x128, encode with sums / decode: 72 / 53 us with one row per wave, 219 / 125 with
+// a launch for each run of one size, 51 / 41 so; the branching kernel alone would
+// take int8 16384 x 896 x 6 from 48 to 52 us).  One buffer range covers the group;
+// lanes past a row's end or past the unit's last row take an offset outside it.
+// Every value and every row's sums are formed by the same operations in the same
+// order as with one row per wave.
 template <int S, int H>
 struct RowGroup {
   static constexpr int kRows = kUnroll / S * H;
-  const CodecUnit *d;
   int64_t row0;    // the group's first row in its unit
   uint32_t n;      // its rows, 1 .. kRows
   uint32_t sub;    // which of a load's rows this lane holds
   uint32_t lane8;  // first column of this lane in a load
-  __device__ __forceinline__ RowGroup(const CodecBatch &b, int64_t g, int lane) {
-    const int u = find_unit(b, g);
-    d = &b.u[u];
-    row0 = (g - b.row_begin[u]) * kRows;
-    const int64_t left = d->rows - row0;
+  __device__ __forceinline__ RowGroup(const CodecUnit &d, int64_t g, int lane) {
+    row0 = g * kRows;
+    const int64_t left = d.rows - row0;
     n = left < kRows ? (uint32_t)left : (uint32_t)kRows;
     sub = H == 2 ? (uint32_t)lane >> 5 : 0u;
     lane8 = (H == 2 ? (uint32_t)lane & 31u : (uint32_t)lane) * 8u;
   }
-  // row (within the group) and column of this lane in load i
+  // row (within the group) and column (of round c0) of this lane in load i
   __device__ __forceinline__ uint32_t row(int i) const { return i / S * H + sub; }
-  __device__ __forceinline__ uint32_t col(int i) const { return i % S * kColsPerStep + lane8; }
-  __device__ __forceinline__ bool in(int i, uint32_t cols) const {
-    return row(i) < n && col(i) < cols;
+  __device__ __forceinline__ uint32_t col(int i, uint32_t c0) const {
+    return c0 + i % S * kColsPerStep + lane8;
+  }
+  __device__ __forceinline__ bool in(int i, uint32_t c0, uint32_t cols) const {
+    return (row(i) < n) & (col(i, c0) < cols);  // no branch between the loads
+  }
+  // Rounds of four loads: one, or over the columns of the single row.  Load i of a
+  // round is skipped by the whole wave where its columns are past the row.
+  template <typename Round>
+  static __device__ __forceinline__ void rounds(uint32_t cols, Round round) {
+    if constexpr (S < kUnroll) round(0u);
+    else for (uint32_t c0 = 0; c0 < cols; c0 += kUnroll * kColsPerStep) round(c0);
+  }
+  static __device__ __forceinline__ bool past(int i, uint32_t c0, uint32_t cols) {
+    return S == kUnroll && c0 + i * kColsPerStep >= cols;
   }
 };
 
@@ -512,81 +524,72 @@ __device__ __forceinline__ float lane_row_sum(float v) {
 constexpr int kGroupThreads = 4 * kWave;
 
 template <int CODE, int BLOCK, bool STATS, int S, int H>
-__global__ __launch_bounds__(kGroupThreads) void compress_rows_kernel(const CodecBatch b) {
+__device__ __forceinline__ void compress_group(const CodecUnit &d, int64_t g, int lane,
+                                               const uint32_t *tab_s, const uint32_t *tab_r) {
   constexpr int kLanesPerBlock = BLOCK / 8;
-  __shared__ uint32_t tab_s[128], tab_r[128];
-  if constexpr (CODE != kCodeCast) {
-    if (threadIdx.x < 128) {
-      tab_s[threadIdx.x] = kQuot<CODE>.s[threadIdx.x];
-      tab_r[threadIdx.x] = kQuot<CODE>.r[threadIdx.x];
-    }
-    __syncthreads();
-  }
-  const int lane = threadIdx.x & (kWave - 1);
-  const int64_t g = (int64_t)blockIdx.x * (kGroupThreads / kWave) +
-                    __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
-  if (g >= b.row_begin[b.n]) return;
-  const RowGroup<S, H> rg(b, g, lane);
-  const CodecUnit &d = *rg.d;
+  const RowGroup<S, H> rg(d, g, lane);
   const uint32_t cols = (uint32_t)d.cols, ld = (uint32_t)d.ld;
   const uint32_t nb = CODE == kCodeCast ? 0u : cols / BLOCK;
   const RowRsrc rx = row_rsrc(d.x + rg.row0 * d.ld, ((rg.n - 1) * ld + cols) * 2);
   const RowRsrc rc = row_rsrc(d.codes + rg.row0 * d.cols, rg.n * cols);
   const RowRsrc rsc = row_rsrc(d.scales + rg.row0 * nb, rg.n * nb * 4);
   const bool leader = (lane & (kLanesPerBlock - 1)) == 0;
-  u32x4 w[kUnroll];
-#pragma unroll
-  for (int i = 0; i < kUnroll; ++i)
-    w[i] = load_b128(rx, rg.in(i, cols) ? (rg.row(i) * ld + rg.col(i)) * 2 : kOutOfRange);
   float acc_x[kUnroll / S] = {}, acc_e[kUnroll / S] = {};
+  rg.rounds(cols, [&](uint32_t c0) {
+    u32x4 w[kUnroll];
 #pragma unroll
-  for (int i = 0; i < kUnroll; ++i) {
-    const bool in = rg.in(i, cols);
-    const uint32_t row = rg.row(i), col = rg.col(i);
-    float x[8], q[8];
-    x[0] = bf16_lo(w[i].x); x[1] = bf16_hi(w[i].x);
-    x[2] = bf16_lo(w[i].y); x[3] = bf16_hi(w[i].y);
-    x[4] = bf16_lo(w[i].z); x[5] = bf16_hi(w[i].z);
-    x[6] = bf16_lo(w[i].w); x[7] = bf16_hi(w[i].w);
-    if constexpr (CODE == kCodeCast) {
-      store_b64(rc, in ? row * cols + col : kOutOfRange, cast8(x, q));
-      if constexpr (STATS) {
+    for (int i = 0; i < kUnroll; ++i)
+      w[i] = load_b128(rx, rg.in(i, c0, cols) ? (rg.row(i) * ld + rg.col(i, c0)) * 2 : kOutOfRange);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const float e = q[j] - x[j];  // exact: both are bf16 values (or NaN)
-          acc_e[i / S] = fmaf(e, e, acc_e[i / S]);
-          acc_x[i / S] = fmaf(x[j], x[j], acc_x[i / S]);
+    for (int i = 0; i < kUnroll; ++i) {
+      if (rg.past(i, c0, cols)) break;
+      const bool in = rg.in(i, c0, cols);
+      const uint32_t row = rg.row(i), col = rg.col(i, c0);
+      float x[8], q[8];
+      x[0] = bf16_lo(w[i].x); x[1] = bf16_hi(w[i].x);
+      x[2] = bf16_lo(w[i].y); x[3] = bf16_hi(w[i].y);
+      x[4] = bf16_lo(w[i].z); x[5] = bf16_hi(w[i].z);
+      x[6] = bf16_lo(w[i].w); x[7] = bf16_hi(w[i].w);
+      if constexpr (CODE == kCodeCast) {
+        store_b64(rc, in ? row * cols + col : kOutOfRange, cast8(x, q));
+        if constexpr (STATS) {
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            const float e = q[j] - x[j];  // exact: both are bf16 values (or NaN)
+            acc_e[i / S] = fmaf(e, e, acc_e[i / S]);
+            acc_x[i / S] = fmaf(x[j], x[j], acc_x[i / S]);
+          }
         }
-      }
-    } else {
-      const uint32_t am = group_max_u32<kLanesPerBlock>(absmax_bf16x8(w[i]));
-      float s, r;
-      uint32_t keep;
-      block_quotients<CODE>(am, tab_s, tab_r, s, r, keep);
-      float v[8];
+      } else {
+        const uint32_t am = group_max_u32<kLanesPerBlock>(absmax_bf16x8(w[i]));
+        float s, r;
+        uint32_t keep;
+        block_quotients<CODE>(am, tab_s, tab_r, s, r, keep);
+        float v[8];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) v[j] = x[j] * r;
-      const u32x2 code = encode8<CODE>(v, keep, q);
-      store_b64(rc, in ? row * cols + col : kOutOfRange, code);
-      store_b32(rsc, in && leader ? (row * nb + col / BLOCK) * 4 : kOutOfRange,
-                __float_as_uint(s));
-      if constexpr (STATS) {
-        // sum x^2 straight from the packed bf16 pairs (products are exact)
-        acc_x[i / S] = dot2_bf16(w[i].x, acc_x[i / S]);
-        acc_x[i / S] = dot2_bf16(w[i].y, acc_x[i / S]);
-        acc_x[i / S] = dot2_bf16(w[i].z, acc_x[i / S]);
-        acc_x[i / S] = dot2_bf16(w[i].w, acc_x[i / S]);
+        for (int j = 0; j < 8; ++j) v[j] = x[j] * r;
+        const u32x2 code = encode8<CODE>(v, keep, q);
+        store_b64(rc, in ? row * cols + col : kOutOfRange, code);
+        store_b32(rsc, in && leader ? (row * nb + col / BLOCK) * 4 : kOutOfRange,
+                  __float_as_uint(s));
+        if constexpr (STATS) {
+          // sum x^2 straight from the packed bf16 pairs (products are exact)
+          acc_x[i / S] = dot2_bf16(w[i].x, acc_x[i / S]);
+          acc_x[i / S] = dot2_bf16(w[i].y, acc_x[i / S]);
+          acc_x[i / S] = dot2_bf16(w[i].z, acc_x[i / S]);
+          acc_x[i / S] = dot2_bf16(w[i].w, acc_x[i / S]);
 #pragma unroll
-        for (int j = 0; j < 8; j += 2) {
-          const uint32_t h = pack_bf16(q[j] * s, q[j + 1] * s);
-          const float e0 = bf16_lo(h) - x[j];
-          const float e1 = bf16_hi(h) - x[j + 1];
-          acc_e[i / S] = fmaf(e0, e0, acc_e[i / S]);
-          acc_e[i / S] = fmaf(e1, e1, acc_e[i / S]);
+          for (int j = 0; j < 8; j += 2) {
+            const uint32_t h = pack_bf16(q[j] * s, q[j + 1] * s);
+            const float e0 = bf16_lo(h) - x[j];
+            const float e1 = bf16_hi(h) - x[j + 1];
+            acc_e[i / S] = fmaf(e0, e0, acc_e[i / S]);
+            acc_e[i / S] = fmaf(e1, e1, acc_e[i / S]);
+          }
         }
       }
     }
-  }
+  });
   if constexpr (STATS) {
 #pragma unroll
     for (int k = 0; k < kUnroll / S; ++k) {
@@ -600,68 +603,116 @@ __global__ __launch_bounds__(kGroupThreads) void compress_rows_kernel(const Code
   }
 }
 
-template <int CODE, int BLOCK, int S, int H>
-__global__ __launch_bounds__(kGroupThreads) void decompress_rows_kernel(const CodecBatch b) {
+// The wave's group, numbered over all units of the batch.
+__device__ __forceinline__ int64_t group_slot() {
+  return (int64_t)blockIdx.x * (kGroupThreads / kWave) +
+         __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+}
+
+template <int CODE, int BLOCK, bool STATS, int RPW>
+__global__ __launch_bounds__(kGroupThreads) void compress_rows_kernel(const CodecBatch b) {
+  __shared__ uint32_t tab_s[128], tab_r[128];
+  if constexpr (CODE != kCodeCast) {
+    if (threadIdx.x < 128) {
+      tab_s[threadIdx.x] = kQuot<CODE>.s[threadIdx.x];
+      tab_r[threadIdx.x] = kQuot<CODE>.r[threadIdx.x];
+    }
+    __syncthreads();
+  }
   const int lane = threadIdx.x & (kWave - 1);
-  const int64_t g = (int64_t)blockIdx.x * (kGroupThreads / kWave) +
-                    __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+  int64_t g = group_slot();
   if (g >= b.row_begin[b.n]) return;
-  const RowGroup<S, H> rg(b, g, lane);
-  const CodecUnit &d = *rg.d;
+  const int u = find_unit(b, g);
+  const CodecUnit d = b.u[u];
+  g -= b.row_begin[u];
+  // all of it now, not behind the branch
+  asm volatile("" ::"s"(d.x), "s"(d.codes), "s"(d.scales), "s"(d.ss_x), "s"(d.ss_err),
+               "s"(d.rows), "s"(d.cols), "s"(d.ld), "s"(g));
+  switch (RPW >= 0 ? RPW : d.rpw_log2) {
+    case 0: compress_group<CODE, BLOCK, STATS, 4, 1>(d, g, lane, tab_s, tab_r); return;
+    case 1: compress_group<CODE, BLOCK, STATS, 2, 1>(d, g, lane, tab_s, tab_r); return;
+    case 2: compress_group<CODE, BLOCK, STATS, 1, 1>(d, g, lane, tab_s, tab_r); return;
+    default: compress_group<CODE, BLOCK, STATS, 1, 2>(d, g, lane, tab_s, tab_r); return;
+  }
+}
+
+template <int CODE, int BLOCK, int S, int H>
+__device__ __forceinline__ void decompress_group(const CodecUnit &d, int64_t g, int lane) {
+  const RowGroup<S, H> rg(d, g, lane);
   const uint32_t cols = (uint32_t)d.cols;
   const uint32_t nb = CODE == kCodeCast ? 0u : cols / BLOCK;
   const RowRsrc rc = row_rsrc(d.codes + rg.row0 * d.cols, rg.n * cols);
   const RowRsrc rsc = row_rsrc(d.scales + rg.row0 * nb, rg.n * nb * 4);
   const RowRsrc rh = row_rsrc(d.xhat + rg.row0 * d.cols, rg.n * cols * 2);
-  u32x2 c[kUnroll];
-  float s[kUnroll];
+  rg.rounds(cols, [&](uint32_t c0) {
+    u32x2 c[kUnroll];
+    float s[kUnroll];
 #pragma unroll
-  for (int i = 0; i < kUnroll; ++i) {
-    const bool in = rg.in(i, cols);
-    c[i] = load_b64(rc, in ? rg.row(i) * cols + rg.col(i) : kOutOfRange);
-    if constexpr (CODE != kCodeCast)
-      s[i] = __uint_as_float(
-          load_b32(rsc, in ? (rg.row(i) * nb + rg.col(i) / BLOCK) * 4 : kOutOfRange));
-  }
-#pragma unroll
-  for (int i = 0; i < kUnroll; ++i) {
-    u32x4 h;
-    if constexpr (CODE == kCodeCast) {
-      h = u32x4{uncast2<false>(c[i].x), uncast2<true>(c[i].x), uncast2<false>(c[i].y),
-                uncast2<true>(c[i].y)};
-    } else {
-      float q[8];
-      decode8<CODE>(c[i], q);
-      h.x = pack_bf16(q[0] * s[i], q[1] * s[i]);
-      h.y = pack_bf16(q[2] * s[i], q[3] * s[i]);
-      h.z = pack_bf16(q[4] * s[i], q[5] * s[i]);
-      h.w = pack_bf16(q[6] * s[i], q[7] * s[i]);
+    for (int i = 0; i < kUnroll; ++i) {
+      const bool in = rg.in(i, c0, cols);
+      c[i] = load_b64(rc, in ? rg.row(i) * cols + rg.col(i, c0) : kOutOfRange);
+      if constexpr (CODE != kCodeCast)
+        s[i] = __uint_as_float(
+            load_b32(rsc, in ? (rg.row(i) * nb + rg.col(i, c0) / BLOCK) * 4 : kOutOfRange));
     }
-    store_b128(rh, rg.in(i, cols) ? (rg.row(i) * cols + rg.col(i)) * 2 : kOutOfRange, h);
+#pragma unroll
+    for (int i = 0; i < kUnroll; ++i) {
+      if (rg.past(i, c0, cols)) break;
+      u32x4 h;
+      if constexpr (CODE == kCodeCast) {
+        h = u32x4{uncast2<false>(c[i].x), uncast2<true>(c[i].x), uncast2<false>(c[i].y),
+                  uncast2<true>(c[i].y)};
+      } else {
+        float q[8];
+        decode8<CODE>(c[i], q);
+        h.x = pack_bf16(q[0] * s[i], q[1] * s[i]);
+        h.y = pack_bf16(q[2] * s[i], q[3] * s[i]);
+        h.z = pack_bf16(q[4] * s[i], q[5] * s[i]);
+        h.w = pack_bf16(q[6] * s[i], q[7] * s[i]);
+      }
+      store_b128(rh, rg.in(i, c0, cols) ? (rg.row(i) * cols + rg.col(i, c0)) * 2 : kOutOfRange, h);
+    }
+  });
+}
+
+template <int CODE, int BLOCK, int RPW>
+__global__ __launch_bounds__(kGroupThreads) void decompress_rows_kernel(const CodecBatch b) {
+  const int lane = threadIdx.x & (kWave - 1);
+  int64_t g = group_slot();
+  if (g >= b.row_begin[b.n]) return;
+  const int u = find_unit(b, g);
+  const CodecUnit d = b.u[u];
+  g -= b.row_begin[u];
+  // all of it now, not behind the branch
+  asm volatile("" ::"s"(d.codes), "s"(d.scales), "s"(d.xhat), "s"(d.rows), "s"(d.cols), "s"(g));
+  switch (RPW >= 0 ? RPW : d.rpw_log2) {
+    case 0: decompress_group<CODE, BLOCK, 4, 1>(d, g, lane); return;
+    case 1: decompress_group<CODE, BLOCK, 2, 1>(d, g, lane); return;
+    case 2: decompress_group<CODE, BLOCK, 1, 1>(d, g, lane); return;
+    default: decompress_group<CODE, BLOCK, 1, 2>(d, g, lane); return;
   }
 }
 
-// Launches a grouped kernel picked by the batch's rows per wave.
+// Launches the kernel of the batch's rows per wave.
 template <int CODE, int BLOCK>
 hipError_t launch_grouped(const CodecBatch &b, bool encode, hipStream_t s) {
   const int per_wg = kGroupThreads / kWave;
   const dim3 grid((unsigned)((b.row_begin[b.n] + per_wg - 1) / per_wg)), block(kGroupThreads);
-  auto pick = [&](auto two, auto four, auto eight) {
+  auto pick = [&](auto two, auto four, auto eight, auto mixed) {
     if (b.rpw_log2 == 1) hipLaunchKernelGGL(two, grid, block, 0, s, b);
     else if (b.rpw_log2 == 2) hipLaunchKernelGGL(four, grid, block, 0, s, b);
-    else hipLaunchKernelGGL(eight, grid, block, 0, s, b);
+    else if (b.rpw_log2 == 3) hipLaunchKernelGGL(eight, grid, block, 0, s, b);
+    else hipLaunchKernelGGL(mixed, grid, block, 0, s, b);
   };
   if (!encode)
-    pick(decompress_rows_kernel<CODE, BLOCK, 2, 1>, decompress_rows_kernel<CODE, BLOCK, 1, 1>,
-         decompress_rows_kernel<CODE, BLOCK, 1, 2>);
+    pick(decompress_rows_kernel<CODE, BLOCK, 1>, decompress_rows_kernel<CODE, BLOCK, 2>,
+         decompress_rows_kernel<CODE, BLOCK, 3>, decompress_rows_kernel<CODE, BLOCK, -1>);
   else if (b.stats)
-    pick(compress_rows_kernel<CODE, BLOCK, true, 2, 1>,
-         compress_rows_kernel<CODE, BLOCK, true, 1, 1>,
-         compress_rows_kernel<CODE, BLOCK, true, 1, 2>);
+    pick(compress_rows_kernel<CODE, BLOCK, true, 1>, compress_rows_kernel<CODE, BLOCK, true, 2>,
+         compress_rows_kernel<CODE, BLOCK, true, 3>, compress_rows_kernel<CODE, BLOCK, true, -1>);
   else
-    pick(compress_rows_kernel<CODE, BLOCK, false, 2, 1>,
-         compress_rows_kernel<CODE, BLOCK, false, 1, 1>,
-         compress_rows_kernel<CODE, BLOCK, false, 1, 2>);
+    pick(compress_rows_kernel<CODE, BLOCK, false, 1>, compress_rows_kernel<CODE, BLOCK, false, 2>,
+         compress_rows_kernel<CODE, BLOCK, false, 3>, compress_rows_kernel<CODE, BLOCK, false, -1>);
   return hipGetLastError();
 }
 
@@ -679,7 +730,7 @@ Launch launch_shape(const CodecBatch &b) {
 
 template <int CODE, int BLOCK>
 hipError_t compress_dispatch(const CodecBatch &b, hipStream_t s) {
-  if (b.rpw_log2 > 0) return launch_grouped<CODE, BLOCK>(b, true, s);
+  if (b.rpw_log2 != 0) return launch_grouped<CODE, BLOCK>(b, true, s);
   const Launch l = launch_shape(b);
   if (b.stats)
     hipLaunchKernelGGL((compress_kernel<CODE, BLOCK, true>), l.grid, l.block, 0, s, b);
@@ -690,7 +741,7 @@ hipError_t compress_dispatch(const CodecBatch &b, hipStream_t s) {
 
 template <int CODE, int BLOCK>
 hipError_t decompress_dispatch(const CodecBatch &b, hipStream_t s) {
-  if (b.rpw_log2 > 0) return launch_grouped<CODE, BLOCK>(b, false, s);
+  if (b.rpw_log2 != 0) return launch_grouped<CODE, BLOCK>(b, false, s);
   const Launch l = launch_shape(b);
   hipLaunchKernelGGL((decompress_kernel<CODE, BLOCK>), l.grid, l.block, 0, s, b);
   return hipGetLastError();
@@ -720,7 +771,7 @@ hipError_t decompress_code(const CodecBatch &b, int block, hipStream_t s) {
 
 hipError_t launch_compress(const CodecBatch &b, int code, int block, hipStream_t s) {
   if (code == kCodeCast) {
-    if (b.rpw_log2 > 0) return launch_grouped<kCodeCast, 256>(b, true, s);  // BLOCK unused
+    if (b.rpw_log2 != 0) return launch_grouped<kCodeCast, 256>(b, true, s);  // BLOCK unused
     const Launch l = launch_shape(b);
     if (b.stats)
       hipLaunchKernelGGL((cast_kernel<true>), l.grid, l.block, 0, s, b);
@@ -734,7 +785,7 @@ hipError_t launch_compress(const CodecBatch &b, int code, int block, hipStream_t
 
 hipError_t launch_decompress(const CodecBatch &b, int code, int block, hipStream_t s) {
   if (code == kCodeCast) {
-    if (b.rpw_log2 > 0) return launch_grouped<kCodeCast, 256>(b, false, s);
+    if (b.rpw_log2 != 0) return launch_grouped<kCodeCast, 256>(b, false, s);
     const Launch l = launch_shape(b);
     hipLaunchKernelGGL(uncast_kernel, l.grid, l.block, 0, s, b);
     return hipGetLastError();

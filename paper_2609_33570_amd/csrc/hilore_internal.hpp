@@ -22,6 +22,7 @@ struct CodecUnit {
   int64_t rows;
   int64_t cols;
   int64_t ld;
+  int rpw_log2;  // log2 of the rows per wave, 0..3
 };
 
 // Units encoded/decoded by one launch travel by value in the kernel
@@ -39,11 +40,11 @@ constexpr int64_t kElemsPerLaunch = int64_t(1) << 28;
 constexpr int64_t kMaxCodecCols = int64_t(1) << 30;
 struct CodecBatch {
   CodecUnit u[kUnitsPerLaunch];
-  int64_t row_begin[kUnitsPerLaunch + 1];  // prefix sum of rows over u[]
+  int64_t row_begin[kUnitsPerLaunch + 1];  // prefix sum over u[] of rows, or of groups of rows
   int n;
   int stats;     // compress: write row sums
   int wpr_log2;  // log2 of the waves per row, 0..4
-  int rpw_log2;  // log2 of the rows per wave, 0..3; above 0 row_begin counts groups of rows
+  int rpw_log2;  // the units' rows per wave (0: row_begin counts rows, else groups), -1: they differ
 };
 
 // Waves per row (as log2, 0..4) for rows of `cols` columns: the fewest that
@@ -63,15 +64,40 @@ inline int codec_wpr_log2(int64_t cols, int lane_steps) {
 // Rows per wave (as log2) for narrow rows.  A wave issues four loads of 512
 // columns at once; a row of up to 1024 columns fills half of them or less, and
 // a wave that moves 1-3 KB and ends leaves the memory idle (16384 x 512 x 8
-// units: encode 62 us, decode 45, against 33 at the copy rate).  So a wave takes
-// 2, 4 or 8 such rows: as many as four loads hold, two rows to a load up to 256
-// columns.  Only in calls of enough rows that the chip stays full with fewer
-// waves, only whole 8-column pieces (rows of the literal cast may end anywhere),
-// and strides that keep a group's byte offsets in 32 bits.
-constexpr int64_t kGroupedRows = 8192;
-inline int codec_rpw_log2(int64_t cols, int64_t ld, int64_t call_rows) {
-  if (call_rows < kGroupedRows || cols % 8 != 0 || ld > (int64_t(1) << 24)) return 0;
+// units, one row per wave: encode 60 us, decode 44, against 33 at the copy rate).
+// So a wave takes 2, 4 or 8 such rows: as many as four loads hold, two rows to a
+// load up to 256 columns.  Only whole 8-column pieces (rows of the literal cast may end anywhere)
+// and strides that keep a group's byte offsets in 32 bits.  fp8 1x128, encode with
+// sums / decode, one row per wave -> grouped: 16384 x 256 x 8 units 57 -> 21 / 39 ->
+// 19 us, 16384 x 512 x 8 60 -> 38 / 44 -> 34, 16384 x 896 x 6 57 -> 48 / 44 -> 44
+// (16, 33 and 43 us at the copy rate).
+inline int codec_rpw_log2(int64_t cols, int64_t ld) {
+  if (cols % 8 != 0 || ld > (int64_t(1) << 24)) return 0;
   return cols <= 256 ? 3 : cols <= 512 ? 2 : cols <= 1024 ? 1 : 0;
+}
+
+// Numbers the rows of a batch, or its groups of rows where its narrow units hold
+// enough of them that the chip stays full with fewer waves (fewer narrow rows gain
+// less than the batch's other units lose: 15 units of 1024 x 2048 and one of 1024 x
+// 128 decode in 17.8 us by rows and 18.4 by groups).  `strided`: the call reads x,
+// whose rows may be padded.
+constexpr int64_t kGroupedRows = 8192;
+inline void codec_number_rows(CodecBatch &b, bool strided) {
+  int64_t narrow = 0;
+  for (int i = 0; i < b.n; ++i) {
+    CodecUnit &u = b.u[i];
+    u.rpw_log2 = codec_rpw_log2(u.cols, strided ? u.ld : u.cols);
+    if (u.rpw_log2 > 0) narrow += u.rows;
+  }
+  int64_t next = 0;
+  for (int i = 0; i < b.n; ++i) {
+    CodecUnit &u = b.u[i];
+    if (narrow < kGroupedRows) u.rpw_log2 = 0;
+    b.rpw_log2 = i == 0 || b.rpw_log2 == u.rpw_log2 ? u.rpw_log2 : -1;
+    b.row_begin[i] = next;
+    next += (u.rows + (int64_t(1) << u.rpw_log2) - 1) >> u.rpw_log2;
+  }
+  b.row_begin[b.n] = next;
 }
 
 hipError_t launch_compress(const CodecBatch &b, int code, int block, hipStream_t s);

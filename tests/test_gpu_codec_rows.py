@@ -74,3 +74,30 @@ def test_groups_match_single_rows(hl, code, block, widths, stats):
             if k not in ("ss_x", "ss_err") or stats:
                 w = u[k + "_buf"]
                 assert bool((w[:GUARD] == 77).all()) and bool((w[-GUARD:] == 77).all())
+
+
+@pytest.mark.parametrize("code,block", [(0, 64), (1, 128), (2, 0)], ids=["int8", "e4m3fn", "cast"])
+@pytest.mark.parametrize("shapes", [
+    [(5001, 896), (4099, 640)],            # every unit two rows per wave,
+    [(4097, 512), (4098, 384)],            # four,
+    [(8193, 128), (1, 256)],               # eight
+    [(4097, 128), (2, 2560), (4099, 1024), (3, 2048), (1003, 1152), (7, 2688), (5, 256),
+     (9001, 896), (1, 384)],               # all sizes and single rows, two row mappings
+], ids=["two", "four", "eight", "mixed"])
+def test_launches_of_one_size_and_of_several(hl, code, block, shapes):
+    many = [make(r, c, block, c, 10 * i + code) for i, (r, c) in enumerate(shapes)]
+    few = [make(r, c, block, c, 10 * i + code) for i, (r, c) in enumerate(shapes)]
+    units = [desc(hl, u, 0, u["rows"], block, True) for u in many]
+    hl.hilore_compress(units, code, block)
+    hl.hilore_decompress(units, code, block)
+    for u in few:
+        for r0 in range(0, u["rows"], 4096):
+            part = [desc(hl, u, r0, min(u["rows"], r0 + 4096), block, True)]
+            hl.hilore_compress(part, code, block)
+            hl.hilore_decompress(part, code, block)
+    for u, v in zip(many, few):
+        for k in OUT:
+            a, b = (t[k + "_buf"].view(torch.uint8) for t in (u, v))
+            assert torch.equal(a, b), (u["rows"], u["cols"], k)
+            w = u[k + "_buf"]
+            assert bool((w[:GUARD] == 77).all()) and bool((w[-GUARD:] == 77).all())
