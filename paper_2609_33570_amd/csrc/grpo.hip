@@ -13,7 +13,8 @@
 // Each workgroup of grpo_kernel owns a run of 1024 consecutive token slots
 // (4 per thread, 128-bit loads), from 2^20 slots on two runs (the group
 // statistics, the count and the launch ramp are then paid half as often; four
-// runs leave too few loads in flight).  At 2^22 masked slots with K3 and N
+// runs leave too few loads in flight) unless the operands are far larger than the
+// caches (see launch_grpo).  At 2^22 masked slots with K3 and N
 // counted, in a graph: 28.3 us with one run, 64-bit indices, a division per slot
 // and expm1f throughout (then bound by its vector instructions), 19.4 us now, 23.0
 // with four runs; 92 MB at the copy rate take 15.  It first forms, with wave
@@ -47,7 +48,8 @@ constexpr int kSlotsPerThread = 4;
 constexpr int kSlotsPerBlock = kThreads * kSlotsPerThread;
 constexpr int kCountThreads = 1024;  // pre-pass: 2^16 slots are four mask words per thread
 constexpr int kCountBatch = 4;
-constexpr int64_t kTwoRunSlots = int64_t(1) << 20;  // from here on two runs per workgroup
+constexpr int64_t kTwoRunSlots = int64_t(1) << 20;  // from here on two runs per workgroup,
+constexpr int64_t kOneRunBytes = int64_t(576) << 20;  // and one again from these operands on
 constexpr int kMaskBatch = 8;  // 16-byte mask words per thread in flight while counting
 static_assert(kGrpoCounts <= kThreads, "one pre-pass count per thread");
 
@@ -117,19 +119,18 @@ __device__ __forceinline__ float expm1_near0(float x) {
   return fmaf(x * x, p, x);
 }
 
-// Outputs of large calls (U > 1) stream past the caches, which leaves more of
-// them to the inputs: 2^22 slots 21.7 -> 19.3 us, 2^24 76 -> 72 us (inputs
-// loaded non-temporally too: 21.9 and 69).
+// Outputs of large calls (NT) stream past the caches, which leaves more of them to
+// the inputs: 2^22 slots with K3, mask and ratio 21.3 -> 19.3 us, 2^24 75 -> 61.
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-template <int U, typename T, typename V>
+template <bool NT, typename T, typename V>
 __device__ __forceinline__ void store(T *p, V v) {
-  if constexpr (U > 1) __builtin_nontemporal_store(v, reinterpret_cast<V *>(p));
+  if constexpr (NT) __builtin_nontemporal_store(v, reinterpret_cast<V *>(p));
   else *reinterpret_cast<V *>(p) = v;
 }
 
 // One workgroup owns U runs of kSlotsPerBlock slots.  Indices fit 32 bits
 // (fewer than 2^31 slots; unsigned sums of a run stay below 2^32).
-template <int U>
+template <int U, bool NT>
 __global__ __launch_bounds__(kThreads) void grpo_kernel(const GrpoArgs a, int p2) {
   constexpr uint32_t kRun = U * kSlotsPerBlock;
   __shared__ float adv_lds[kRun + 2];  // responses overlapping the runs (T >= 1)
@@ -299,9 +300,9 @@ __global__ __launch_bounds__(kThreads) void grpo_kernel(const GrpoArgs a, int p2
       fl |= f << (8 * k);
     }
     if (i0 + kSlotsPerThread <= c1) {
-      store<U>(a.coeff + i0, f32x4{om[0], om[1], om[2], om[3]});
-      if (a.ratio) store<U>(a.ratio + i0, f32x4{rat[0], rat[1], rat[2], rat[3]});
-      store<U>(a.flags + i0, fl);
+      store<NT>(a.coeff + i0, f32x4{om[0], om[1], om[2], om[3]});
+      if (a.ratio) store<NT>(a.ratio + i0, f32x4{rat[0], rat[1], rat[2], rat[3]});
+      store<NT>(a.flags + i0, fl);
     } else {
 #pragma unroll
       for (int k = 0; k < kSlotsPerThread; ++k) {
@@ -346,13 +347,23 @@ hipError_t launch_grpo(const GrpoArgs &a, uint32_t *counts, hipStream_t s) {
       b.n_counts = nb;
     }
   }
-  // two runs per workgroup need the pre-pass (or no count), and the chip full
-  // with half the workgroups: at 2^20 slots 512 of them
-  const bool two = slots >= kTwoRunSlots && (b.counts || !a.mask || !a.count_mask);
+  // Two runs per workgroup need the pre-pass (or no count), and the chip full with
+  // half the workgroups: at 2^20 slots 512 of them.  Once the operands are more than
+  // twice the 256 MB cache, calls with logp_ref or ratio run slower in pairs: 2^26
+  // masked slots, N given, 248 us with one run and 264 with two (K3 and ratio), 198 and
+  // 212 (K3), 199 and 214 (ratio); 2^25 131 / 134, 104 / 107, 102 / 107; 2^24 55 / 56,
+  // 47.5 / 46.5, 48 / 46.  The line lies at 18 bytes for 2^25 slots: 17 bytes (ratio
+  // without a mask) still take 89 / 85.  Without both operands pairs stay ahead or
+  // close (2^26 unmasked slots 163 / 151, masked 179 / 169 counted, 155 / 163 given).
+  const bool large = slots >= kTwoRunSlots;
+  const int64_t bytes = 13 + (a.mask ? 1 : 0) + (a.logp_ref ? 4 : 0) + (a.ratio ? 4 : 0);
+  const bool single = (a.logp_ref || a.ratio) && slots * bytes >= kOneRunBytes;
+  const bool two = large && !single && (b.counts || !a.mask || !a.count_mask);
   const int64_t run = kSlotsPerBlock * (two ? 2 : 1);
   const dim3 grid((unsigned)((slots + run - 1) / run));
-  if (two) hipLaunchKernelGGL(grpo_kernel<2>, grid, dim3(kThreads), 0, s, b, p2);
-  else hipLaunchKernelGGL(grpo_kernel<1>, grid, dim3(kThreads), 0, s, b, p2);
+  if (two) hipLaunchKernelGGL((grpo_kernel<2, true>), grid, dim3(kThreads), 0, s, b, p2);
+  else if (large) hipLaunchKernelGGL((grpo_kernel<1, true>), grid, dim3(kThreads), 0, s, b, p2);
+  else hipLaunchKernelGGL((grpo_kernel<1, false>), grid, dim3(kThreads), 0, s, b, p2);
   return hipGetLastError();
 }
 

@@ -27,6 +27,7 @@ def call(hl, rew, new, old, ref, mask, P, G, T, n_norm):
     (4096, 4, 65),        # responses across threads, a last workgroup of one run and a bit
     (65600, 16, 1),       # one slot per response: every slot of a thread another response
     (8, 5, 26217),        # runs inside one response, odd total
+    (1025, 32, 1025),     # operands past twice the cache: one run again, odd total
 ])
 def test_two_runs_match_one(hl, P, G, T):
     g = torch.Generator(device="cuda").manual_seed(P + G + T)
