@@ -508,9 +508,9 @@ hipError_t launch_allocate(const AllocArgs &a, int KB, int KD, void *workspace, 
       hipLaunchKernelGGL(kernel, gd, bd, 0, s, src, dst, pr, uc + i, words, chunks, recip,
                          (uint32_t)grid, KB, KD, guard);
     };
-    if (g == 1) launch(dpn_kernel<1>);
-    else if (g == 2) launch(dpn_kernel<2>);
-    else launch(dpn_kernel<3>);
+    static_assert(kDpGroup == 2);
+    if (g == 2) launch(dpn_kernel<2>);
+    else launch(dpn_kernel<1>);
   }
   const int n_partial = grid < kPartials ? grid : kPartials;
   hipLaunchKernelGGL(terminal_partial_kernel, dim3(n_partial), dim3(kDpThreads), 0, s,
