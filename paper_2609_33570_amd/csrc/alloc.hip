@@ -16,7 +16,7 @@
 // units updates the whole grid, one thread per cell (rows k of risk cost,
 // columns j of memory cost, a row padded to a multiple of 64 cells so that a wave
 // covers 64 consecutive cells of one row; each XCD takes one contiguous band of
-// cells: 734 -> 834 us for 196 units without).  Each cell forms the first unit's
+// cells: 100 us less of a call with 196 units).  Each cell forms the first unit's
 // value at itself and at the two cells the second unit's actions shift it to,
 // from up to nine cells of the table before the pair (fp64, all in the 256 MB
 // infinity cache for grids up to a few thousand squared), and writes the value
@@ -167,10 +167,11 @@ constexpr int ipow3(int n) { return n == 0 ? 1 : 3 * ipow3(n - 1); }
 // the L2s (17.8 MB, cold in every launch) on top of the launch itself: 6.3 us a
 // pair of units on the 1025 x 1025 grid, of which 2.8 are left on a grid a
 // sixteenth of it.  With a 64-bit division, a branch and a wait per source the
-// chain of dependent loads came on top (7.2 us).  Measured and not better: 3
-// units a launch (27 sources: 758 against 683 us for 196 units; better only on
-// small grids), one unit (1004), 2, 3 or 6 chunks a wave (883 to 1211: longer
-// code, fetched cold by every launch), workgroups of 128 and 1024 threads.
+// chain of dependent loads came on top (7.2 us).  A call with 196 units takes 653
+// us.  Measured and not better, in us more of that call: 3 units a launch (27
+// sources: 75; better only on small grids), one unit (320), 2, 3 or 6 chunks a
+// wave (200 to 530: longer code, fetched cold by every launch), workgroups of 128
+// and 1024 threads.
 template <int N>
 __global__ __launch_bounds__(kDpThreads) void dpn_kernel(
     const double *__restrict__ prev, double *__restrict__ cur, uint64_t *__restrict__ pred,
@@ -240,7 +241,7 @@ __global__ __launch_bounds__(kDpThreads) void dpn_kernel(
       f[t] = max_f64(rh, vl);
     }
   // Written through at device scope: a table left dirty in the L2s is flushed at
-  // the launch's end, with every CU idle (731 -> 679 us for 196 units).
+  // the launch's end, with every CU idle (52 us more of a call with 196 units).
   __hip_atomic_store(reinterpret_cast<double *>(reinterpret_cast<char *>(cur) + cell8), f[0],
                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (lane == 0) {

@@ -44,7 +44,8 @@ struct CodecBatch {
   int n;
   int stats;     // compress: write row sums
   int wpr_log2;  // log2 of the waves per row, 0..4
-  int rpw_log2;  // the units' rows per wave (0: row_begin counts rows, else groups), -1: they differ
+  int rpw_log2;  // the units' rows per wave (0: row_begin counts rows, else groups); -1 where
+                 // they differ
 };
 
 // Waves per row (as log2, 0..4) for rows of `cols` columns: the fewest that
@@ -66,11 +67,11 @@ inline int codec_wpr_log2(int64_t cols, int lane_steps) {
 // a wave that moves 1-3 KB and ends leaves the memory idle (16384 x 512 x 8
 // units, one row per wave: encode 60 us, decode 44, against 33 at the copy rate).
 // So a wave takes 2, 4 or 8 such rows: as many as four loads hold, two rows to a
-// load up to 256 columns.  Only whole 8-column pieces (rows of the literal cast may end anywhere)
-// and strides that keep a group's byte offsets in 32 bits.  fp8 1x128, encode with
-// sums / decode, one row per wave -> grouped: 16384 x 256 x 8 units 57 -> 21 / 39 ->
-// 19 us, 16384 x 512 x 8 60 -> 38 / 44 -> 34, 16384 x 896 x 6 57 -> 48 / 44 -> 44
-// (16, 33 and 43 us at the copy rate).
+// load up to 256 columns.  Only whole 8-column pieces (rows of the literal cast
+// may end anywhere) and strides that keep a group's byte offsets in 32 bits.  fp8
+// 1x128, encode with sums / decode, one row per wave -> grouped: 16384 x 256 x 8
+// units 57 -> 21 / 39 -> 19 us, 16384 x 512 x 8 60 -> 38 / 44 -> 34, 16384 x 896 x 6
+// 57 -> 48 / 44 -> 44 (16, 33 and 43 us at the copy rate).
 inline int codec_rpw_log2(int64_t cols, int64_t ld) {
   if (cols % 8 != 0 || ld > (int64_t(1) << 24)) return 0;
   return cols <= 256 ? 3 : cols <= 512 ? 2 : cols <= 1024 ? 1 : 0;

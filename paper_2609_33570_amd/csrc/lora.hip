@@ -59,14 +59,16 @@
 // 16384 x 18944 85 / 92 / 98 against 90 / 95 / 111, 13001 x 3584 23 / 25 / 27
 // against 25 / 27 / 31.
 //
-// Passes of 65 .. 80 rows (R = 5): lora_coop_kernel (the slab kernel would need
-// 280 registers; spilling it takes 128 us against 116 on 16384 x 18944).  The
-// workgroup walks its k-steps in order, two per barrier: every thread loads 16 code bytes of each (D k-steps in flight in registers) and
-// dequantises them once into a double-buffered [64][256] bf16 tile in LDS,
-// the dh block goes to LDS next to it, and wave w runs the MFMAs of column
-// groups 2w and 2w+1 (16 columns each, B operand by transposing reads of the
-// tile) for all R row blocks.  Each wave owns its columns, so a segment ends
-// with plain stores of the partial and no cross-wave reduction.
+// Passes of 65 .. 80 rows (R = 5), and of 33 .. 64 with few k-steps a workgroup
+// (see few_steps): lora_coop_kernel (at R = 5 the slab kernel would need 280
+// registers; spilling it takes 128 us against 116 on 16384 x 18944).  The
+// workgroup walks its k-steps in order, two per barrier: every thread loads 16
+// code bytes of each (D k-steps in flight in registers) and dequantises them once
+// into a double-buffered [64][256] bf16 tile in LDS, the dh block goes to LDS next
+// to it, and wave w runs the MFMAs of column groups 2w and 2w+1 (16 columns each,
+// B operand by transposing reads of the tile) for all R row blocks.  Each wave
+// owns its columns, so a segment ends with plain stores of the partial and no
+// cross-wave reduction.
 #include "device_common.hpp"
 #include "hilore_internal.hpp"
 
@@ -540,7 +542,8 @@ __global__ __launch_bounds__(kThreads, 1) void lora_slab_kernel(const LoraArgs a
   SlabPlan<BLOCK, R, WIDE> p;
 #pragma unroll
   for (int i = 0; i < p.kDhLoads; ++i)
-    p.vo_d[i] = WIDE ? dh_offset(a, lane + 64 * i, 2 * R, 8) : dh_offset(a, lane + 64 * i, 8 * R, 2);
+    p.vo_d[i] = WIDE ? dh_offset(a, lane + 64 * i, 2 * R, 8)
+                     : dh_offset(a, lane + 64 * i, 8 * R, 2);
 
   int seg = 0;
   // at most two segments per range (the plan keeps n_wg >= S)
@@ -844,8 +847,8 @@ __global__ __launch_bounds__(256) void lora_reduce_kernel(const LoraArgs a) {
     const float *at = a.part + rr * kStrip + c4 + w0 * step;
     sum = *reinterpret_cast<const f32x4 *>(range_begin(a, w0) < first ? at + slot : at);
     at += step;
-    // up to 16 partials per round trip (a narrow unit's strip has up to 18
-    // parts); the additions stay in ascending workgroup order
+    // up to 16 partials per round trip; the additions stay in ascending workgroup
+    // order (a narrow unit's strip has at most 256 / S parts, of 8 k-steps or more)
     for (int64_t w = w0 + 1; w <= w1; w += kReduceBatch, at += kReduceBatch * step) {
       f32x4 x[kReduceBatch];
 #pragma unroll
@@ -867,6 +870,19 @@ __global__ __launch_bounds__(256) void lora_reduce_kernel(const LoraArgs a) {
   }
 }
 
+// Whether a pass of 33 .. 64 rows takes the cooperative kernel, on units that are not
+// split into equal parts (32 strips or more, or less than 481 tokens): with few k-steps
+// a workgroup the slab kernel's sums over its pairs at every segment end cost more than
+// its loads gain, twice so where ranges cross strips.  fp8 1x128, r = 48 / 64,
+// cooperative against slab: 1024 x 8192 (4 k-steps) 17.4 / 20.1 against 18.0 / 21.3 us,
+// 2048 x 8192 (8) 19.9 / 22.4 against 18.9 / 21.9; ranges that cross: 1024 x 14336 (7)
+// 23.0 / 25.5 against 24.2 / 27.6, 2048 x 12288 (12) 23.9 / 27.3 against 24.2 / 27.9,
+// 1500 x 18944 (14) 27.0 / 30.1 against 26.5 / 29.7; int8 1x64, 300 x 3584 (1) 12.5 / 13.9
+// against 12.8 / 14.7.
+bool few_steps(const LoraArgs &a) {
+  return a.slots == 2 && a.U <= (a.n_wg % a.S == 0 ? 5 : 12) * a.n_wg;
+}
+
 template <int CODE, int BLOCK, bool WIDE>
 void launch_main(const LoraArgs &a, hipStream_t s) {
   const dim3 grid((unsigned)a.n_wg), block(kThreads);
@@ -878,10 +894,16 @@ void launch_main(const LoraArgs &a, hipStream_t s) {
       hipLaunchKernelGGL((lora_slab_kernel<CODE, BLOCK, 2, WIDE>), grid, block, 0, s, a);
       return;
     case 3:
-      hipLaunchKernelGGL((lora_slab_kernel<CODE, BLOCK, 3, WIDE>), grid, block, 0, s, a);
+      if (few_steps(a))
+        hipLaunchKernelGGL((lora_coop_kernel<CODE, BLOCK, 3, WIDE>), grid, block, 0, s, a);
+      else
+        hipLaunchKernelGGL((lora_slab_kernel<CODE, BLOCK, 3, WIDE>), grid, block, 0, s, a);
       return;
     case 4:
-      hipLaunchKernelGGL((lora_slab_kernel<CODE, BLOCK, 4, WIDE>), grid, block, 0, s, a);
+      if (few_steps(a))
+        hipLaunchKernelGGL((lora_coop_kernel<CODE, BLOCK, 4, WIDE>), grid, block, 0, s, a);
+      else
+        hipLaunchKernelGGL((lora_slab_kernel<CODE, BLOCK, 4, WIDE>), grid, block, 0, s, a);
       return;
     default:
       hipLaunchKernelGGL((lora_coop_kernel<CODE, BLOCK, 5, WIDE>), grid, block, 0, s, a);
@@ -920,29 +942,36 @@ LoraPlan lora_plan(int64_t K, int64_t M, int r) {
   const int widest = pass_blocks(r < kRows * kMaxR ? r : kRows * kMaxR);
   p.slots = 2;
   // Narrow units (fewer than 32 strips, e.g. a hidden-width input): every strip
-  // is split into `parts` equal ranges, one per workgroup, so no range crosses a
-  // strip (one partial each).  A range is whole rounds of the kernel's k-steps,
-  // the fewest that S * parts <= 256 workgroups allow, and `parts` the smallest
-  // count that reaches them.  A round is two k-steps of every wave of the per-wave
-  // kernel (16) or pair of the slab kernel (8), and 4 k-steps for the cooperative
-  // one: on 13001 x 3584 rounds of 16 leave 74 of 256 CUs without a workgroup,
-  // finer ones 18 (fp8 1x128, r = 32 / 48 / 64 / 80: 23.0 / 25.0 / 26.7 / 32.3 ->
-  // 21.1 / 23.5 / 25.6 / 29.6 us; with one adapter block finer rounds gain on some
-  // sizes and lose on others, 19.5 -> 18.6 us on 10007 x 3584, 14.3 -> 17.2 on
-  // 16384 x 896).
-  const int64_t per = widest == 1 ? 2 * kWaves : widest < kMaxR ? 2 * kPairs : kPairs;
+  // is split into `parts` equal ranges (to one k-step), one per workgroup, so no
+  // range crosses a strip (one partial each).  The longest range is a whole number
+  // of rounds of the kernel's k-steps, the fewest that S * parts <= 256 workgroups
+  // allow, and `parts` the smallest count that reaches them.  A round is two k-steps
+  // of every wave of the per-wave kernel (16) or pair of the slab kernel (8), and 4
+  // k-steps for the cooperative one: on 13001 x 3584 rounds of 16 leave 74 of 256
+  // CUs without a workgroup, finer ones 18 (fp8 1x128, r = 32 / 48 / 64 / 80: 23.0 /
+  // 25.0 / 26.7 / 32.3 -> 21.1 / 23.5 / 25.6 / 29.6 us; with one adapter block finer
+  // rounds gain on some sizes and lose on others, 19.5 -> 18.6 us on 10007 x 3584,
+  // 14.3 -> 17.2 on 16384 x 896).
+  // Ranges of 8 k-steps become ranges of 16 where there would be many of them: each
+  // costs a partial sum of 16 KB per row block, written and read, and every 16 on a
+  // strip another round trip of the reduction.  8 -> 16 k-steps, r = 32 / 48 / 64 / 80:
+  // 16384 x 896 16.1 / 19.4 / 21.2 / 24.3 -> 13.6 / 15.7 / 18.1 / 23.3 us, 4096 x 3584
+  // 13.2 / 17.1 / 19.1 / 23.0 -> 12.9 / 14.8 / 18.3 / 22.3; on the other side of the
+  // lines 4096 x 1280 10.8 / 12.4 / 13.9 against 11.4 / 12.9 / 14.3, 2048 x 3584 11.0 /
+  // 12.8 / 15.0 against 11.6 / 13.1 / 14.9, 8192 x 1024 at r = 80 18.9 against 19.9.
+  // (8 at least: one partial a workgroup then needs no more workspace than two of
+  // ranges of 16.)
   if (p.S < 32 && p.KS >= 2 * kWaves) {
-    // count in whole rounds of `step` k-steps, at most `most` of them
-    auto split = [&](int64_t step, int64_t most) {
-      const int64_t rounds = (p.KS + step * most - 1) / (step * most);
-      return (p.KS + step * rounds - 1) / (step * rounds);
-    };
     const int64_t pmax = kLoraWorkgroups / p.S;
-    // at most twice the parts of 16 k-steps: short units gain nothing from more
-    // partial sums, and one partial each then never needs more workspace than two
-    const int64_t cap = 2 * split(2 * kWaves, pmax);
-    const int64_t parts = split(per, cap < pmax ? cap : pmax);
-    p.n_wg = p.S * parts;
+    const int64_t per = widest == 1 ? 2 * kWaves : widest < kMaxR ? 2 * kPairs : kPairs;
+    int64_t rounds = (p.KS + per * pmax - 1) / (per * pmax);
+    if (rounds * per <= 8) {
+      const int64_t p8 = (p.KS + 7) / 8;
+      const bool many = widest < kMaxR ? p.S * p8 * p8 > 2048
+                                       : p.S * p8 > 128 || p.S * p8 * p8 > 8000;
+      rounds = (many ? 16 : 8) / per;
+    }
+    p.n_wg = p.S * ((p.KS + per * rounds - 1) / (per * rounds));
     p.slots = 1;
   }
   p.workspace_bytes = (size_t)(p.n_wg > 0 ? p.n_wg : 1) * (size_t)p.slots *

@@ -200,8 +200,9 @@ def _desc_array(units: Sequence[hilore_unit_desc]):
 def _workspace(workspace, nbytes: int, stream):
     """(pointer, size) of a caller's workspace tensor; without one, a fresh
     device buffer of the queried size (torch's allocator; no call reads what a
-    workspace holds on entry) when any is needed.  torch reuses a freed buffer in the order of its current stream, so
-    a call on another stream must bring its own workspace."""
+    workspace holds on entry) when any is needed.  torch reuses a freed buffer in the
+    order of its current stream, so a call on another stream must bring its own
+    workspace."""
     if workspace is None:
         if nbytes == 0:
             return None, 0, None

@@ -181,3 +181,21 @@ def test_wgrad_out_of_memory(fake, kw):
 def test_wgrad_on_the_per_thread_stream(fake):
     """One handle stands for a stream of every thread: no order among its calls."""
     assert fake(stream=2) == ("unsplit", None, 2) and not fake.state["taken"]
+
+
+def test_lora_workspace_never_above_two_partials_of_16_steps():
+    """Narrow units keep one partial a workgroup; however finely they are split, no call asks for
+    more than two partials a workgroup of ranges of whole rounds of 16 k-steps take."""
+    import random
+
+    rng = random.Random(5)
+    for _ in range(20000):
+        K, M = int(2 ** rng.uniform(9, 18)), 16 * rng.randrange(1, 31 * 16 + 1)
+        r = 2 * rng.randrange(1, 60)
+        S, KS = -(-M // 256), -(-K // 32)
+        most = 256 // S
+        rounds = -(-KS // (16 * most))
+        parts = -(-KS // (16 * rounds))
+        blocks = -(-min(r, 80) // 16)
+        assert hilore.hilore_lora_grad_workspace_bytes(K, M, r) <= 2 * S * parts * blocks * 16384, \
+            (K, M, r)

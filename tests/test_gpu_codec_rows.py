@@ -101,3 +101,25 @@ def test_launches_of_one_size_and_of_several(hl, code, block, shapes):
             assert torch.equal(a, b), (u["rows"], u["cols"], k)
             w = u[k + "_buf"]
             assert bool((w[:GUARD] == 77).all()) and bool((w[-GUARD:] == 77).all())
+
+
+def test_cast_rows_of_any_length_share_a_launch(hl):
+    """Rows of the literal cast may end inside an 8-column piece; such a unit keeps one row
+    per wave in a launch whose other units are grouped."""
+    shapes = [(8200, 128), (333, 13), (1001, 896), (7, 2001), (65, 1023), (4099, 264)]
+    many = [make(r, c, 0, -(-c // 8) * 8, 10 * i) for i, (r, c) in enumerate(shapes)]
+    few = [make(r, c, 0, -(-c // 8) * 8, 10 * i) for i, (r, c) in enumerate(shapes)]
+    units = [desc(hl, u, 0, u["rows"], 0, True) for u in many]
+    hl.hilore_compress(units, 2, 0)
+    hl.hilore_decompress(units, 2, 0)
+    for u in few:
+        for r0 in range(0, u["rows"], 4096):
+            part = [desc(hl, u, r0, min(u["rows"], r0 + 4096), 0, True)]
+            hl.hilore_compress(part, 2, 0)
+            hl.hilore_decompress(part, 2, 0)
+    for u, v in zip(many, few):
+        for k in OUT:
+            a, b = (t[k + "_buf"].view(torch.uint8) for t in (u, v))
+            assert torch.equal(a, b), (u["rows"], u["cols"], k)
+            w = u[k + "_buf"]
+            assert bool((w[:GUARD] == 77).all()) and bool((w[-GUARD:] == 77).all())

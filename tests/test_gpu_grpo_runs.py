@@ -64,6 +64,10 @@ def test_expm1_range(hl):
         new = torch.zeros(n, device="cuda")
         rew = torch.ones(16, device="cuda")
         out = call(hl, rew, new, new.clone(), x.contiguous(), None, 1, 16, n // 16, 1.0)
-        want = -1e-3 * torch.expm1(x.double())
-        # beta in fp32, expm1 within an ulp, two roundings
-        assert bool(((out["coeff"].double() - want).abs() <= 2.0 ** -22 * want.abs()).all())
+        beta = float(torch.tensor(1e-3, dtype=torch.float32))
+        want = -beta * torch.expm1(x.double())
+        # equal rewards and N = 1: the coefficient is -beta e, rounded once (half an ulp), with
+        # e within 0.86 ulp of expm1 where the polynomial forms it and within 1.5 elsewhere
+        # (an ulp of a float is at most 2^-23 of it)
+        ulps = torch.where(x.abs() <= 0.5, 0.86 + 0.5, 1.5 + 0.5)
+        assert bool(((out["coeff"].double() - want).abs() <= ulps * 2.0 ** -23 * want.abs()).all())

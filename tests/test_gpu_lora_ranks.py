@@ -47,3 +47,18 @@ def test_integer_exact(hl, code, block, K, M, r):
     assert torch.equal(da.double(), want)
     hl.hilore_dequant_lora_grad(codes, scales, code, block, dh, da, K, M, r, 2.0, True, ws)
     assert torch.equal(da.double(), 2 * want)
+
+
+@pytest.mark.parametrize("r", [34, 48, 64, 80])
+@pytest.mark.parametrize("code,block,K,M", [
+    (1, 128, 2049, 1152),   # 5 strips: ranges of 8 k-steps
+    (0, 64, 8200, 1152),    # ranges of 16, an odd number of k-steps
+    (2, 0, 16385, 272),     # 2 strips, 33 parts each
+    (0, 32, 160, 8192),     # 32 strips, one k-step or none a workgroup: cooperative to 64 rows
+    (1, 64, 1400, 9728),    # 38 strips, ranges across strips, cooperative
+    (1, 128, 4099, 8448),   # 33 strips, ranges across strips, slab
+    (0, 256, 1500, 16384),  # 64 strips of four ranges each, slab
+])
+def test_splits(hl, code, block, K, M, r):
+    """Both kernels of 33 to 64 rows and every rule of the split, no more workspace than asked."""
+    test_integer_exact(hl, code, block, K, M, r)

@@ -180,6 +180,10 @@ def test_out_of_memory(hl):
     try:
         torch.cuda.set_per_process_memory_fraction(
             (torch.cuda.memory_reserved() + 1) / torch.cuda.mem_get_info()[1])
+        need, held = hl.hilore_wgrad_workspace_bytes(K, M, N), []
+        with pytest.raises(torch.cuda.OutOfMemoryError):  # what earlier tests left in the pool
+            while True:
+                held.append(torch.empty(need, dtype=torch.uint8, device="cuda"))
         with pytest.warns(RuntimeWarning, match="unsplit"):
             hl.hilore_dequant_wgrad(codes, scales, 1, 128, dy, dw, K, M, N)
     finally:
