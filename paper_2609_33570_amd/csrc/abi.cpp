@@ -580,6 +580,7 @@ hilore_status hilore_dequant_lora_grad(const void *x_codes, const float *x_scale
   a.n_wg = plan.n_wg;
   a.xcd_remap = plan.xcd_remap;
   a.slots = plan.slots;
+  a.whole_parts = plan.whole_parts;
   return hip_status(hilore::launch_lora(a, code, block, r, static_cast<hipStream_t>(stream)));
 }
 

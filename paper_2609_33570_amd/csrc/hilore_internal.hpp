@@ -242,7 +242,8 @@ struct LoraPlan {
   int64_t S, KS, U;  // strips of 256 columns, k-steps of 32 rows per strip, S * KS
   int64_t n_wg;      // workgroups of the main kernel
   int xcd_remap;     // give each XCD consecutive ranges
-  int slots;         // partials per workgroup: 2 where its range may meet two strips
+  int slots;         // partial slots per workgroup: 2 where its range may meet two strips
+  int whole_parts;   // every strip split into equal ranges, none across strips
   size_t workspace_bytes;
   int passes;        // 16 adapter rows per pass
 };
@@ -258,7 +259,8 @@ struct LoraArgs {
   float scale;
   int accumulate;
   int64_t S, KS, U, n_wg;
-  int xcd_remap, slots;
+  int64_t step;  // floats between the first partials of two workgroups (set per pass)
+  int xcd_remap, slots, whole_parts;
 };
 hipError_t launch_lora(const LoraArgs &a, int code, int block, int r, hipStream_t s);
 

@@ -359,7 +359,7 @@ __global__ __launch_bounds__(kThreads, 1) void lora_wave_kernel(const LoraArgs a
         *reinterpret_cast<f32x4 *>(&mine[(4 * h + v) * kStrip + 16 * q + 4 * c4]) =
             f32x4{acc[4 * c4][v], acc[4 * c4 + 1][v], acc[4 * c4 + 2][v], acc[4 * c4 + 3][v]};
     __syncthreads();
-    float *out = a.part + (a.slots * wg + seg) * (int64_t)kPart;
+    float *out = a.part + wg * a.step + seg * (int64_t)kPart;
 #pragma unroll
     for (int e4 = 0; e4 < kPart / 4 / kThreads; ++e4) {
       const int e = 4 * (tid + e4 * kThreads);
@@ -588,7 +588,7 @@ __global__ __launch_bounds__(kThreads, 1) void lora_slab_kernel(const LoraArgs a
 
     // acc[rb][c][v] = dA[16 rb + 4h + v][128 half + 8 q + c] of this wave's
     // k-steps; the four pairs are added in order, one row block at a time
-    float *out = a.part + (a.slots * wg + seg) * kSlot;
+    float *out = a.part + wg * a.step + seg * kSlot;
 #pragma unroll
     for (int rb = 0; rb < R; ++rb) {
       float *mine = red[wave];
@@ -804,7 +804,7 @@ __global__ __launch_bounds__(kThreads, 1) void lora_coop_kernel(const LoraArgs a
     // segment writes them
     __syncthreads();
     // acc[rb][gi][v] = dA[16 rb + 4 h + v][16 (2 wave + gi) + q]
-    float *out = a.part + (a.slots * wg + seg) * kSlot;
+    float *out = a.part + wg * a.step + seg * kSlot;
 #pragma unroll
     for (int rb = 0; rb < R; ++rb)
 #pragma unroll
@@ -826,7 +826,7 @@ __global__ __launch_bounds__(kThreads, 1) void lora_coop_kernel(const LoraArgs a
 // earlier strip, and then holds this strip's sums in its second slot.
 constexpr int kReduceBatch = 16;
 
-// SLOTS: partials per workgroup (a.slots; as a load it cost every call 0.2 us).
+// SLOTS: a.slots (the step between partials as a load cost every call 0.2 us).
 template <int SLOTS>
 __global__ __launch_bounds__(256) void lora_reduce_kernel(const LoraArgs a) {
   const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -880,7 +880,7 @@ __global__ __launch_bounds__(256) void lora_reduce_kernel(const LoraArgs a) {
 // 1500 x 18944 (14) 27.0 / 30.1 against 26.5 / 29.7; int8 1x64, 300 x 3584 (1) 12.5 / 13.9
 // against 12.8 / 14.7.
 bool few_steps(const LoraArgs &a) {
-  return a.slots == 2 && a.U <= (a.n_wg % a.S == 0 ? 5 : 12) * a.n_wg;
+  return !a.whole_parts && a.U <= (a.n_wg % a.S == 0 ? 5 : 12) * a.n_wg;
 }
 
 template <int CODE, int BLOCK, bool WIDE>
@@ -940,6 +940,7 @@ LoraPlan lora_plan(int64_t K, int64_t M, int r) {
   p.xcd_remap = p.n_wg % 8 == 0 && p.S >= 32 ? 1 : 0;
   // passes of up to 80 adapter rows; the widest sets the partial slot size
   const int widest = pass_blocks(r < kRows * kMaxR ? r : kRows * kMaxR);
+  p.passes = (r + kRows * kMaxR - 1) / (kRows * kMaxR);
   p.slots = 2;
   // Narrow units (fewer than 32 strips, e.g. a hidden-width input): every strip
   // is split into `parts` equal ranges (to one k-step), one per workgroup, so no
@@ -960,7 +961,7 @@ LoraPlan lora_plan(int64_t K, int64_t M, int r) {
   // lines 4096 x 1280 10.8 / 12.4 / 13.9 against 11.4 / 12.9 / 14.3, 2048 x 3584 11.0 /
   // 12.8 / 15.0 against 11.6 / 13.1 / 14.9, 8192 x 1024 at r = 80 18.9 against 19.9.
   // (8 at least: one partial a workgroup then needs no more workspace than two of
-  // ranges of 16.)
+  // ranges of 16 k-steps, which is what these calls have always asked for at most.)
   if (p.S < 32 && p.KS >= 2 * kWaves) {
     const int64_t pmax = kLoraWorkgroups / p.S;
     const int64_t per = widest == 1 ? 2 * kWaves : widest < kMaxR ? 2 * kPairs : kPairs;
@@ -971,12 +972,19 @@ LoraPlan lora_plan(int64_t K, int64_t M, int r) {
                                        : p.S * p8 > 128 || p.S * p8 * p8 > 8000;
       rounds = (many ? 16 : 8) / per;
     }
-    p.n_wg = p.S * ((p.KS + per * rounds - 1) / (per * rounds));
-    p.slots = 1;
+    const int64_t parts = (p.KS + per * rounds - 1) / (per * rounds);
+    p.n_wg = p.S * parts;
+    p.whole_parts = 1;
+    // Where several passes write partials (r > 80), a gap as wide as a partial between
+    // them is 3 to 6% faster (16384 x 2048, r = 128: 48.9 -> 45.9 us, 8192 x 3584 48.0 ->
+    // 45.6); a single pass gains and loses a few per cent by it.  It is left where it
+    // asks for no more workspace than two partials of ranges of 16 k-steps.
+    const int64_t rounds16 = (p.KS + 16 * pmax - 1) / (16 * pmax);
+    const int64_t parts16 = (p.KS + 16 * rounds16 - 1) / (16 * rounds16);
+    p.slots = p.passes > 1 && parts <= parts16 ? 2 : 1;
   }
-  p.workspace_bytes = (size_t)(p.n_wg > 0 ? p.n_wg : 1) * (size_t)p.slots *
-                      (size_t)(kRows * widest * kStrip) * sizeof(float);
-  p.passes = (r + kRows * kMaxR - 1) / (kRows * kMaxR);
+  p.workspace_bytes = (size_t)(p.n_wg > 0 ? p.n_wg : 1) *
+                      (size_t)(p.slots * kRows * widest * kStrip) * sizeof(float);
   return p;
 }
 
@@ -985,6 +993,7 @@ hipError_t launch_lora(const LoraArgs &base, int code, int block, int r, hipStre
     LoraArgs a = base;
     a.r0 = r0;
     a.r_pass = r - r0 < kRows * kMaxR ? r - r0 : kRows * kMaxR;
+    a.step = (int64_t)a.slots * kRows * pass_blocks(a.r_pass) * kStrip;
     if (a.U > 0) {
       if (code == kCodeCast) launch_main<kCodeCast, 256>(a, s);  // no blocks; BLOCK unused
       else if (code == kCodeInt8) dispatch<kCodeInt8>(a, block, s);
@@ -992,8 +1001,8 @@ hipError_t launch_lora(const LoraArgs &base, int code, int block, int r, hipStre
     }
     const int64_t threads = a.S * a.r_pass * (kStrip / 4);
     const dim3 grid((unsigned)((threads + 255) / 256));
-    if (a.slots == 1) hipLaunchKernelGGL(lora_reduce_kernel<1>, grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL(lora_reduce_kernel<2>, grid, dim3(256), 0, s, a);
+    auto reduce = a.slots == 1 ? lora_reduce_kernel<1> : lora_reduce_kernel<2>;
+    hipLaunchKernelGGL(reduce, grid, dim3(256), 0, s, a);
   }
   return hipGetLastError();
 }
