@@ -548,6 +548,11 @@ hipError_t dispatch(const WgradArgs &a, int block, hipStream_t s) {
 // Unsplit -> split, fp8 1x128, us a call: 11987x3584x512 266 -> 58,
 // 16384x3584x18944 2143 -> 1862, 16384x896x4864 333 -> 157,
 // 1024x896x256 28 -> 19; 1024x3584x512 would stay at 29.
+// The constants are those of the fp8 1x128 kernel.  The int8 kernel takes the same
+// time and the cast kernel, which has no scales, 2 to 6% less, so one plan serves all
+// three (25 shapes, int8 / fp8 / cast: 16384x896x256 308 -> 33 / 308 -> 33 / 301 -> 32,
+// 2048x3584x512 50 -> 34 / 50 -> 34 / 49 -> 33; least gains 4096x4096x14336 465 -> 455 /
+// 460 -> 456 / 432 -> 426, 16384x4096x14336 1715 -> 1680 / 1688 -> 1653 / 1585 -> 1574).
 WgradPlan wgrad_plan(int64_t K, int64_t M, int64_t N) {
   constexpr double kStageUs = 1.25, kBusyUs = 0.5, kFillUs = 8.0, kReduceUs = 8.0, kSlotUs = 0.06;
   WgradPlan p{};
